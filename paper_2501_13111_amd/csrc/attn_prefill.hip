@@ -47,6 +47,7 @@
 
 #include "fp_device.h"
 #include "fp_internal.h"
+#include "lds_copy.h"
 
 namespace fpk {
 
@@ -54,31 +55,6 @@ constexpr int PK = 32;          // keys per block (= VT_BLK: one value-cache blo
 
 __device__ __forceinline__ uint32_t mul_f16x2(uint32_t x, uint32_t y) {
     return __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, x) * __builtin_bit_cast(f16x2, y));
-}
-
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-
-// The four words of a raw buffer resource over [base, base + bytes): no stride, 32-bit data
-// format (the resource __builtin_amdgcn_make_buffer_rsrc builds), for copies written in asm.
-__device__ __forceinline__ i32x4 rsrc_words(const void* base, uint32_t bytes) {
-    const uint64_t p = (uint64_t)base;
-    return i32x4{(int32_t)(uint32_t)p, (int32_t)((uint32_t)(p >> 32) & 0xFFFFu), (int32_t)bytes, 0x00020000};
-}
-
-// Buffer-to-LDS copy: lane l's W bytes (16 or 4) at voff + soff of the resource land at LDS
-// address lds + W l (past the resource's end: zeros).  M0 carries the LDS address and is
-// restored afterwards; one wait state separates its write from the copy.
-template <int W>
-__device__ __forceinline__ void lds_copy(const i32x4& r, uint32_t voff, uint32_t soff, uint32_t lds) {
-    uint32_t keep;
-    if constexpr (W == 16)
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dwordx4 %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(keep) : "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
-    else
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %1\n\ts_nop 0\n\t"
-                     "buffer_load_dword %2, %3, %4 offen lds\n\ts_mov_b32 m0, %0"
-                     : "=&s"(keep) : "s"(lds), "v"(voff), "s"(r), "s"(soff) : "memory");
 }
 
 template <int D, bool KV8, int NW, int HPW>

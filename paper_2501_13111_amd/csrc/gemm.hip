@@ -23,14 +23,16 @@
 //    2 x 2, each 64 (32) x 64; the next K tiles are loaded into a ring of registers
 //    (and dequantised on the way to LDS) while the current one is multiplied;
 //  * large problems: 256 x 256 tiles, 8 waves in 2 x 4, each 128 x 64, operands
-//    copied global -> LDS by buffer loads that write LDS directly, two LDS stages.
-// Both multiply with 32x32x16 MFMAs, which run at about 1.4x the rate of 16x16x32
-// on this part.
+//    copied global -> LDS by buffer loads that write LDS directly; two groups of waves
+//    take turns at reading fragments and multiplying (gemm_big_kernel).
 // Both map workgroups to tiles XCD-aware: workgroups are dealt to the 8 XCDs
 // round-robin, and each XCD takes a contiguous range of a grouped raster so its
 // L2 sees the same A row tiles and weight column tiles again.
+#include <type_traits>
+
 #include "fp_device.h"
 #include "fp_internal.h"
+#include "lds_copy.h"
 
 namespace fpk {
 
@@ -39,8 +41,7 @@ constexpr int GBN = 128, GBK = 64, GPAD = 8;
 #define GEMM_BIG_MIN_TILES 128   // 256 x 256 tiles from this many
 #endif
 #ifndef GEMM_GM
-#define GEMM_GM 2                // tile rows per group of the grouped raster (256-row tiles: a
-                                 // group keeps 2 activation row-tiles per XCD in flight)
+#define GEMM_GM 2                // tile rows per group of the small tiling's grouped raster
 #endif
 #ifndef GEMM_SMALL_TILES
 #define GEMM_SMALL_TILES 256
@@ -332,44 +333,78 @@ hipError_t launch_gemm_small(const GemmArgs& a, int wf, int epi, hipStream_t st)
 
 
 // ---------------------------------------------------------------------------
-// Large prefill GEMMs: 256 x 256 tiles, 8 waves of 128 x 64 (4 x 2 32x32 MFMA tiles),
-// operands copied global -> LDS by buffer loads that write LDS directly (16 B per
-// lane), two LDS stages; the next stage's copies are issued in parts between the
-// MFMA steps of the first half of the current stage.  A rows are stored with an XOR swizzle of their 16-byte
-// chunks so that MFMA fragment reads are free of bank conflicts; weight blocks
-// keep their fragment-major order, so a fragment is one contiguous 1 KiB read.
-// Quantised weights stay packed in LDS and are converted to fp16 per fragment.  For the
-// int4 qkv projection (fp32 output, whose K / V rows become cache codes) the fragments hold
-// the exact integers q - z, and the group scale goes to the fp32 accumulators instead: a
-// stage is one 128-input group, and a lane's accumulators of a 32x32 tile all belong to
-// one output column (one scale), so before each stage the lane re-expresses them in units
-// of that stage's scale (acc *= s_prev / s_cur) and the epilogue multiplies by the last
-// one; no weight is rounded to fp16.  The other int4 projections (o, [gate; up], down)
-// multiply the exact q - z by the group scale in fp16 instead -- the dequantised weight
-// rounded once to fp16, relative error at most 2^-11 -- which takes one packed multiply
-// per two weights instead of the rescaling of 128 accumulators per lane every stage.  The
-// fragments take one shift per word (i4x8_to_f16x8_q).
+// Large prefill GEMMs: 256 x 256 tiles, 8 waves of 128 x 64 (8 x 4 16x16 MFMA tiles), K in
+// slices of 32.
+//
+// What bounds it: the package power limit.  On operands of real data the part clocks the
+// matrix cores at 1.7-2.0 GHz, and a loop of MFMAs on registers alone sustains 1.71 PFLOP/s
+// with 32x32x16 and 1.97 with 16x16x32 (both 2.46 on zeros, at 2.4 GHz); with one
+// wave tile's LDS reads beside them, 1.42 and 1.54.  16x16x32 moves a quarter as many
+// accumulator values per MFMA through the register file for half the operations, so it takes
+// less power for the same work, and the kernel uses it.  Consecutive MFMAs
+// share one operand throughout (columns of a row left to right, the next row right to left),
+// measured 1% faster again.
+//
+// Schedule: the 4 waves of the upper 128 rows and those of the lower 128 (one of each per
+// SIMD) run half a slice apart.  A wave alternates a memory phase (its slice's LDS reads and
+// its share of the copies of the slice three ahead) and a compute phase (32 MFMAs at raised
+// priority, the unpacking of quantised weights between them); a barrier ends each phase, so
+// on every SIMD one wave's MFMAs cover the other's reads and address arithmetic.
+// Operands go global -> LDS by buffer copies written in asm with exact wait counts (the
+// compiler would wait for every copy before each LDS read).  A ring of four 32-k activation
+// slices (rows of 64 B, 16-byte chunks XOR-swizzled so fragment reads meet no bank
+// conflict) and a ring of weight K-steps (4 of 32 k for bf16, 3 of 64 k for int8, 2 of 128 k
+// for int4), fragment-major as in memory: quantised weights stay packed in LDS, and a lane
+// reads exactly the codes of its own fragment (8 or 4 bytes; the 64 lanes together one
+// contiguous run).
+//
+// Measured against the kernel it replaced (32x32x16, all waves in step, one barrier per 64 or
+// 128 k), both run for 0.35 s after 0.25 s of warm-up, TFLOP/s: bf16 131072 x 7168 x 8192
+// 1285 -> 1435; int4 131072 x 7168 x 8192 1230 -> 1377, 32768 x 27648 x 5120 1205 -> 1347,
+// 4096 x 27648 x 5120 1185 -> 1324, 32768 x 5120 x 13824 with its residual 1261 -> 1371;
+// int8 8192 x 22016 x 4096 1236 -> 1344; exact int4 32768 x 15360 x 5120 1233 -> 1244 (the
+// rescaling, 128 multiplies per 128 MFMAs, is not covered).
+//
+// For the int4 qkv projection (fp32 output, whose K / V rows become cache codes) the fragments
+// hold the exact integers q - z, and the group scale goes to the fp32 accumulators instead:
+// a lane's accumulators of a 16-column tile all belong to one output column (one scale),
+// so before each 128-input group the lane re-expresses them in units of that group's
+// scale (acc *= s_prev / s_cur) and the epilogue multiplies by the last one; no weight is
+// rounded to fp16.  The other int4 projections (o, [gate; up], down) multiply the exact
+// q - z by the group scale in fp16 instead -- the dequantised weight rounded once to fp16,
+// relative error at most 2^-11 -- which takes one packed multiply per two weights instead of
+// the rescaling of 128 accumulators per lane every group.  The fragments take one shift per
+// word (i4x8_to_f16x8_q).
 
 // int4 projections other than qkv: weights (q - z) * s rounded to fp16 (0: every int4
 // projection takes the exact scheme)
 #ifndef GEMM_FASTQ
 #define GEMM_FASTQ 1
 #endif
+// tile rows per group of the large tiling's raster.  An XCD's 32 workgroups cover 4 x 8 tiles
+// at a time, so a slice of activations is shared by 8 of them and a slice of weights by 4.
+// Against 2 and 8 on the shapes above: within 2% of the best everywhere, where 2 loses up to
+// 5% on wide outputs (27648 columns) and 8 up to 4% on tall ones (131072 rows).
+#ifndef GEMM_BIG_GM
+#define GEMM_BIG_GM 4
+#endif
 constexpr int BT = 256;
 template <int WF>
 struct BigT {
-    static constexpr int TK = (WF == W_INT4) ? 128 : 64;                             // k per stage
+    static constexpr int TK = (WF == W_INT4) ? 128 : 64;                             // K is a multiple of this
     static constexpr int KSW = (WF == W_BF16) ? 32 : (WF == W_INT8 ? 64 : 128);     // weight K-step
-    static constexpr int NBLK = TK / KSW;                                            // blocks per row-block per stage
-    static constexpr int A_BYTES = BT * TK * 2;
-    static constexpr int B_BYTES = 16 * NBLK * 1024;
-    static constexpr int STAGE = A_BYTES + B_BYTES;
-    static constexpr int CPR = TK / 8;                                               // 16-byte chunks per A row
-    static constexpr int NSUB = TK / 32;                                             // MFMA k-steps per stage
-    // LDS: two stages, reused by the epilogue (the residual epilogue stages 8 waves x 64 rows
-    // x 72 floats; one workgroup per CU either way)
-    static constexpr int EPI_BYTES = 8 * 64 * 72 * 4;
-    static constexpr int SMEM = 2 * STAGE > EPI_BYTES ? 2 * STAGE : EPI_BYTES;
+    static constexpr int SPB = KSW / 32;                                             // slices per weight K-step
+    static constexpr int NAS = 4;                                                    // activation slices in the ring
+    static constexpr int NBS = (WF == W_BF16) ? 4 : (WF == W_INT8 ? 3 : 2);          // weight K-steps in the ring
+    static constexpr int A_SLOT = BT * 32 * 2;
+    static constexpr int B_SLOT = 16 * 1024;                                         // 16 row-blocks of one K-step
+    static constexpr int B0 = NAS * A_SLOT;
+    static constexpr int SZ0 = B0 + NBS * B_SLOT;                                    // int4: two groups' scale | zero words
+    static constexpr int RING = SZ0 + (WF == W_INT4 ? 2048 : 0);
+    static constexpr int ES = 68;                                                    // residual staging: row stride (floats)
+    static constexpr int EPI_BYTES = 8 * 64 * ES * 4;
+    // LDS: the rings, reused by the epilogue (one workgroup per CU either way)
+    static constexpr int SMEM = RING > EPI_BYTES ? RING : EPI_BYTES;
 };
 
 // Eight int4 codes of one word (device nibble order) -> exact fp16 q - z, one shift: the
@@ -390,9 +425,6 @@ __device__ __forceinline__ u32x4 i4x8_to_f16x8_q(uint32_t w, f16x2 b1024, f16x2 
     return r;
 }
 
-template <int CPR>
-__device__ __forceinline__ int a_swz(int row) { return CPR == 8 ? ((row >> 1) & 7) : (row & 15); }
-
 template <int WF, int EPI, bool DUAL>
 __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
     using T = BigT<WF>;
@@ -400,7 +432,8 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
     static_assert(DUAL == (EPI == EPI_SWIGLU) || EPI == EPI_PART, "dual tiling");
     __shared__ __attribute__((aligned(1024))) char smem[T::SMEM];
 
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int wm = w >> 2, wn = w & 3;      // 2 x 4 waves, each 128 x 64
     int mt, nt;
@@ -408,7 +441,7 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
         const int Tn = a.tiles_m * a.tiles_n, bid = blockIdx.x;
         const int x = bid & 7, j = bid >> 3, q = Tn >> 3, rm = Tn & 7;
         const int t = x * q + (x < rm ? x : rm) + j;
-        const int GM = GEMM_GM;
+        const int GM = GEMM_BIG_GM;
         const int grp = t / (GM * a.tiles_n);
         const int gm0 = grp * GM;
         const int gsz = min(GM, a.tiles_m - gm0);
@@ -431,275 +464,282 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
             return b;
         }
     };
-    // LDS row-block of this wave's column tile j
+    // LDS row-block of this wave's column tile j (dual: gate, gate, up, up of the same f)
     auto col_rb = [&](int j) -> int {
         if constexpr (DUAL) return j < 2 ? wn * 2 + j : 8 + wn * 2 + (j - 2);
         else return wn * 4 + j;
     };
+    constexpr bool EXQ = WF == W_INT4 && (!GEMM_FASTQ || EPI == EPI_F32);   // int4: exact scheme (qkv)
 
-    uint32_t nsz[2], csz[2];       // int4: scale | zero << 16 of the lane's two columns, next / current stage
-    float s_unit[2] = {1.f, 1.f};  // int4: the scale the lane's accumulators of column tile j are in
-    f16x2 qbias[2], qbias64[2];    // int4: fp16 1024 + z and 64 + z of the current group
-    f16x2 qs2[2];                  // int4, rounded weights: the group scale, twice
-    constexpr bool EXQ = !GEMM_FASTQ || EPI == EPI_F32;   // int4: exact scheme (qkv)
-
-    // Copies of one stage, issued in parts from inside the previous stage's MFMA loop so
-    // that no wave stalls on a burst of copies.  They go through buffer resources: rows
-    // past M and blocks past the matrix read past the resource's end and land as zeros,
-    // so the per-thread source offsets are fixed and only advance with k.
-    constexpr int NA = BT * T::CPR / 512;            // A copies per thread per stage
-    constexpr int NB = 16 * T::NBLK / 8;             // B copies per thread per stage
-    constexpr int NPART = T::TK / 16;                // parts = 16-k MFMA steps of a stage
-    uint32_t aoff[NA];
+    // ---- copies.  Rows past M and blocks past the matrix read past the end of their buffer
+    // resource and land as zeros, and so do slices past the k-range (resource size 0), so every
+    // wave issues the same copies on every trip.  The k advance goes into the resources (base
+    // moved forward, size cut by as much); per-lane offsets are fixed, LDS destinations
+    // wave-uniform.
+    uint32_t aoff[2], boff[2];
 #pragma unroll
-    for (int i = 0; i < NA; ++i) {
-        const int pp = (i * 8 + w) * 64 + lane;
-        const int row = pp / T::CPR, slot = pp % T::CPR;
-        const int kc = (slot ^ a_swz<T::CPR>(row)) * 8;
-        aoff[i] = m0 + row < a.M ? (uint32_t)(((int64_t)(m0 + row) * a.K + kc) * 2) : BUF_OOB;
-    }
-    uint32_t boff[NB];
-#pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int blk = i * 8 + w;
+    for (int i = 0; i < 2; ++i) {
+        // activation piece p: row p / 4; LDS slot p % 4 holds the row's chunk slot ^ ((row / 2) % 4)
+        const int p = (i * 8 + w) * 64 + lane;
+        const int row = p >> 2, ch = (p & 3) ^ ((row >> 1) & 3);
+        aoff[i] = (uint32_t)row * (uint32_t)a.K * 2u + ch * 16;
         bool v;
-        const int gb = grow_block(blk / T::NBLK, v);
-        boff[i] = v ? (uint32_t)((((int64_t)gb * a.kst + blk % T::NBLK) * 64 + lane) * 16) : BUF_OOB;
+        const int gb = grow_block(i * 8 + w, v);
+        boff[i] = v ? (uint32_t)(((int64_t)gb * a.kst * 64 + lane) * 16) : BUF_OOB;
     }
-    // int4: the lane's column of each column tile in the group-major scale / zero words
-    // (-1: past the matrix)
-    int szcol[2] = {-1, -1};
-    if constexpr (WF == W_INT4) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            bool v;
-            const int gb = grow_block(col_rb(2 * j + ((lane & 31) >> 4)), v);
-            szcol[j] = v ? gb * 16 + r : -1;
-        }
-    }
-    // K is a whole number of stages (the launcher sends other K to the small tiling), so
-    // every k of every stage exists: the k advance goes into the buffer resources (uniform:
-    // base moved forward, size cut by as much) and the per-lane offsets stay fixed; the
-    // past-the-end offsets of rows past M and of blocks past the matrix stay past the end.
-    // The LDS destinations are wave-uniform (scalar arithmetic, no per-copy VALU work).
-    const uint32_t xbytes = (uint32_t)min((int64_t)a.M * a.K * 2, (int64_t)0xFFFFFFF0);
+    const char* abase = (const char*)a.X + (int64_t)m0 * a.K * 2;
+    const uint32_t abytes = (uint32_t)min(a.M - m0, BT) * (uint32_t)a.K * 2u;
     const uint32_t wbytes = (uint32_t)min((int64_t)(DUAL ? 2 * nrb : nrb) * a.kst * 1024, (int64_t)0xFFFFFFF0);
-    const int wu = __builtin_amdgcn_readfirstlane(w);
-    auto issue_part = [&](int stage, int k0, int q) {
-        char* sA = smem + stage * T::STAGE;
-        char* sB = sA + T::A_BYTES;
-        const uint32_t xadv = 2u * (uint32_t)k0;
-        const uint32_t wadv = (uint32_t)(k0 / T::KSW) * 1024u;
-        const __amdgpu_buffer_rsrc_t xr = buf_rsrc((const char*)a.X + xadv, xbytes - xadv);
-        const __amdgpu_buffer_rsrc_t wr = buf_rsrc((const char*)a.W + wadv, wbytes - wadv);
-#pragma unroll
-        for (int i = 0; i < NA; ++i)
-            if ((i * NPART) / NA == q) {
-                // through a local: an array element passed straight to the builtin left the
-                // kernels' host stubs unemitted (no diagnostic; the link caught it)
-                const uint32_t off = aoff[i];
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lvoid_t*)(sA + (i * 8 + wu) * 1024), 16, off, 0, 0, 0);
-            }
-#pragma unroll
-        for (int i = 0; i < NB; ++i)
-            if ((i * NPART) / NB == q) {
-                const uint32_t off = boff[i];
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lvoid_t*)(sB + (i * 8 + wu) * 1024), 16, off, 0, 0, 0);
-            }
-        if constexpr (WF == W_INT4) {
-            if (q == 0) {
-                // raw words, not converted here: a conversion would wait for them (and
-                // for the stage's copies issued before them)
-                const uint32_t* szg = a.sz + (int64_t)(k0 / 128) * a.N;
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    nsz[j] = 0u;
-                    if (szcol[j] >= 0) nsz[j] = szg[szcol[j]];
-                }
-            }
-        }
-    };
-    auto issue = [&](int stage, int k0) {
-#pragma unroll
-        for (int q = 0; q < NPART; ++q) issue_part(stage, k0, q);
-    };
-
-    // 32x32 MFMA tiles: 4 (rows) x 2 (columns) per wave.  Column tile j covers the
-    // wave's LDS row-blocks col_rb(2 j) and col_rb(2 j + 1); lane l holds column l % 32.
-    f32x16 acc[4][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f32x16{};
-
-    const int l32 = lane & 31, h32 = lane >> 5;
-    // multiply stage `stage` out of LDS; with nk0 >= 0, issue the copies of the stage at
-    // k offset nk0 into the other buffer, two parts per 16-k step over the first half of
-    // the steps (the second half covers their latency before the stage's closing wait)
-    // int4: the stage is one group; the accumulators go to units of its scale, and the
-    // biases that turn the extracted nibbles into q - z are set (two per column: nibbles in
-    // bits 0-3 of an fp16 half read as 1024 + q, in bits 4-7 with exponent 0x54 as 64 + q)
-    // A group whose scale is zero (its weights dequantise to zero) gets the unit 2^-64: the
-    // accumulators are scaled up by s_prev * 2^64 and the group's own contribution, taken in
-    // that unit, ends up 2^-64 / s_next of the value -- some 1e-18 of it, far below the
-    // accumulators' rounding -- with no per-fragment work.
-    auto regroup = [&]() {
-        if constexpr (!EXQ) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const float z = h2f((uint16_t)(csz[j] >> 16));
-                const _Float16 b0 = (_Float16)(1024.0f + z), b1 = (_Float16)(64.0f + z);
-                qbias[j] = f16x2{b0, b0};
-                qbias64[j] = f16x2{b1, b1};
-                const _Float16 sc = __builtin_bit_cast(_Float16, (uint16_t)(csz[j] & 0xFFFFu));
-                qs2[j] = f16x2{sc, sc};
-            }
-            return;
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const float sc = h2f((uint16_t)(csz[j] & 0xFFFFu));
-            const float s_new = sc == 0.f ? 0x1p-64f : sc;
-            const float ratio = s_unit[j] * __builtin_amdgcn_rcpf(s_new);   // within 1 ulp
-            s_unit[j] = s_new;
-            const float z = h2f((uint16_t)(csz[j] >> 16));
-            const _Float16 b0 = (_Float16)(1024.0f + z), b1 = (_Float16)(64.0f + z);
-            qbias[j] = f16x2{b0, b0};
-            qbias64[j] = f16x2{b1, b1};
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i][j] *= ratio;
-        }
-    };
-    auto compute = [&](int stage, int nk0) {
-        const char* sA = smem + stage * T::STAGE;
-        const char* sB = sA + T::A_BYTES;
-        u32x2 wd2[2];                                        // int4: the 32-k step's two words
-        u32x4 wd4[2];                                        // int8: the 32-k step's 16 codes
-#pragma unroll
-        for (int kk = 0; kk < T::TK / 16; ++kk) {            // 16-k MFMA steps
-            if (nk0 >= 0 && kk < T::TK / 32) {
-                issue_part(stage ^ 1, nk0, 2 * kk);
-                issue_part(stage ^ 1, nk0, 2 * kk + 1);
-            }
-            const int s = kk >> 1, hh = kk & 1;              // 32-k sub-step, half
-            u32x4 af[4], bop[2];
-            // 16-byte chunk of the A row: k 8 c .. 8 c + 7 for chunk c.  int4 lanes take the
-            // k of the weight word they hold (below), so the chunk follows it: the MFMA only needs
-            // both operands to agree on k
-            const int chunk = WF != W_BF16 ? 4 * s + 2 * h32 + hh : 2 * kk + h32;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int row = wm * 128 + 32 * i + l32;
-                af[i] = *(const u32x4*)(sA + row * (T::CPR * 16) + ((chunk ^ a_swz<T::CPR>(row)) * 16));
-            }
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int rb = col_rb(2 * j + (l32 >> 4)), rr = lane & 15;
-                if constexpr (WF == W_BF16) {
-                    // block (rb, s): lane r + 16 g holds k 8 g .. 8 g + 7 of the 32-k step
-                    bop[j] = *(const u32x4*)(sB + (rb * 2 + s) * 1024 + (rr + 16 * (2 * hh + h32)) * 16);
-                } else if constexpr (WF == W_INT8) {
-                    // one 64-k block: lane r + 16 g holds k 16 g .. 16 g + 15.  A lane half h32
-                    // takes piece g = 2 s + h32 whole at the step's first half (k 32 s + 16 h32
-                    // + 8 hh ..): one 16-byte read per 32-k step
-                    if (hh == 0) wd4[j] = *(const u32x4*)(sB + rb * 1024 + (rr + 16 * (2 * s + h32)) * 16);
-                    const u32x2 c = hh ? u32x2{wd4[j].z, wd4[j].w} : u32x2{wd4[j].x, wd4[j].y};
-                    const u32x2 c0 = i8x4_to_f16x4(c.x), c1 = i8x4_to_f16x4(c.y);
-                    bop[j] = u32x4{c0.x, c0.y, c1.x, c1.y};
-                } else {
-                    // one 128-k block: lane r + 16 g holds k 32 g .. 32 g + 31, 8 per dword.  A
-                    // lane half h32 takes words 2 h32 and 2 h32 + 1 of the 32-k step (k 32 s +
-                    // 16 h32 + 8 hh ..), both in one 8-byte read at the step's first half: one LDS
-                    // read where two 4-byte reads at a 16-byte lane stride met bank conflicts.
-                    // Exact q - z
-                    if (hh == 0) wd2[j] = *(const u32x2*)(sB + rb * 1024 + (rr + 16 * s) * 16 + 8 * h32);
-                    const uint32_t wd = hh ? wd2[j].y : wd2[j].x;
-                    bop[j] = i4x8_to_f16x8_q(wd, qbias[j], qbias64[j]);
-                    if constexpr (!EXQ) {
-                        const u32x4 d = bop[j];
-                        bop[j] = u32x4{mul_h2(d.x, qs2[j]), mul_h2(d.y, qs2[j]), mul_h2(d.z, qs2[j]), mul_h2(d.w, qs2[j])};
-                    }
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j) acc[i][j] = mfma32<AF>(af[i], bop[j], acc[i][j]);
-            // quantised weights: the compiler's interleaving strategy 1 for the step's LDS reads,
-            // unpacking and MFMAs (measured 1.5-4% faster; bf16 weights are faster without it)
-            if constexpr (WF != W_BF16) __builtin_amdgcn_iglp_opt(1);
-        }
-    };
+    uint32_t szoff = BUF_OOB;                        // int4: scale | zero word of tile column 64 (w % 4) + lane
+    if constexpr (WF == W_INT4) {
+        const int c = (w & 3) * 64 + lane;
+        bool v;
+        const int gb = grow_block(c >> 4, v);
+        szoff = v ? (uint32_t)(gb * 16 + (c & 15)) * 4u : BUF_OOB;
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(lvoid_t*)smem;
 
     // k-range of this workgroup (the whole of K unless the GEMM is split)
     const int kb = EPI == EPI_PART ? blockIdx.y * a.krange : 0;
     const int ke = EPI == EPI_PART ? min(a.K, kb + a.krange) : a.K;
-    const int nk = (ke - kb + T::TK - 1) / T::TK;
-    issue(0, kb);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        if constexpr (WF == W_INT4) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) csz[j] = nsz[j];
-        }
-        const int nk0 = kt + 1 < nk ? kb + (kt + 1) * T::TK : -1;
-        if constexpr (WF == W_INT4) regroup();
-        compute(kt & 1, nk0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-    }
+    const int ns = (ke - kb) / 32;                   // slices: a multiple of 2, of 4 for int4
 
-    // ---- epilogue (accumulator element e of lane l: row 8 (e / 4) + 4 (l / 32) + e % 4 of
-    // the 32x32 tile, column l % 32)
-    if constexpr (EPI == EPI_PART) {
+    auto copy_a = [&](int s) {
+        const uint32_t adv = (uint32_t)(kb + s * 32) * 2u;
+        const i32x4 rs = rsrc_words(abase + adv, s < ns ? abytes - adv : 0u);
+        const uint32_t dst = lds0 + (uint32_t)(s & 3) * T::A_SLOT + (uint32_t)w * 1024u;
+        lds_copy<16>(rs, aoff[0], 0u, dst);
+        lds_copy<16>(rs, aoff[1], 0u, dst + 8192u);
+    };
+    auto bslot = [&](int q) { return (uint32_t)(T::NBS == 3 ? q % 3 : q & (T::NBS - 1)) * T::B_SLOT; };
+    auto copy_b = [&](int q, int i) {                // half i of weight K-step q of the range
+        const uint32_t adv = (uint32_t)(kb / T::KSW + q) * 1024u;
+        const i32x4 rs = rsrc_words((const char*)a.W + adv, q * T::SPB < ns ? wbytes - adv : 0u);
+        lds_copy<16>(rs, boff[i], 0u, lds0 + T::B0 + bslot(q) + (uint32_t)(i * 8 + w) * 1024u);
+    };
+    auto copy_sz = [&](int q) {                      // waves 4-7 write the same words as waves 0-3
+        const i32x4 rs = rsrc_words(a.sz + (int64_t)(kb / 128 + q) * a.N, q * 4 < ns ? (uint32_t)a.N * 4u : 0u);
+        lds_copy<4>(rs, szoff, 0u, lds0 + T::SZ0 + (uint32_t)(q & 1) * 1024u + (uint32_t)(w & 3) * 256u);
+    };
+    // The copies issued in the memory phase of slice s (u = s % 4): the activations of slice
+    // s + 3, whose ring slot held slice s - 1, and the weights that the rings have room for.
+    // At the end of that phase the wave waits for all but the copies of slices s - 1 and s,
+    // so slice s + 1 (activations copied in phase s - 2, weights two phases ago or more)
+    // is complete for every wave after the barrier.
+    auto issue = [&](int s, int u) {
+        copy_a(s + 3);
+        if constexpr (WF == W_BF16) {
+            copy_b(s + 3, 0);
+            copy_b(s + 3, 1);
+        } else if constexpr (WF == W_INT8) {
+            copy_b(s / 2 + 2, u & 1);                // slot of K-step s / 2 - 1
+        } else {
+            if (u == 0) copy_sz(s / 4 + 1);
+            if (u < 2) copy_b(s / 4 + 1, u);         // slot of K-step s / 4 - 1
+        }
+    };
+
+    f32x4 acc[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float s_unit[4] = {1.f, 1.f, 1.f, 1.f};   // int4 exact: the scale the accumulators of column tile j are in
+    f16x2 qbias[4], qbias64[4];               // int4: fp16 1024 + z and 64 + z of the lane's weight rows
+    f16x2 qs2[4];                             // int4, rounded weights: the group scale, twice
+    u32x4 af[8], bop[4];
+    const char* sAr = smem + (wm * 128 + r) * 64 + ((g ^ ((r >> 1) & 3)) * 16);
+    // the lane's codes of a 32-k fragment (weight row r, k 8 g .. 8 g + 7) inside a block
+    const int blane = WF == W_BF16 ? lane * 16 : WF == W_INT8 ? (r + 16 * (g >> 1)) * 16 + 8 * (g & 1) : r * 16 + 4 * g;
+    const char* sBr = smem + T::B0 + blane;
+
+    // A group whose scale is zero (its weights dequantise to zero) gets the unit 2^-64: the
+    // accumulators are scaled up by s_prev * 2^64 and the group's own contribution, taken in
+    // that unit, ends up 2^-64 / s_next of the value -- some 1e-18 of it, far below the
+    // accumulators' rounding -- with no per-fragment work.
+    float ratio[4];                           // int4 exact: s_prev / s_cur of the group that starts
+    auto regroup = [&](int q) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t sz = *(const uint32_t*)(smem + T::SZ0 + (q & 1) * 1024 + (col_rb(j) * 16 + r) * 4);
+            const float z = h2f((uint16_t)(sz >> 16));
+            const _Float16 b0 = (_Float16)(1024.0f + z), b1 = (_Float16)(64.0f + z);
+            qbias[j] = f16x2{b0, b0};
+            qbias64[j] = f16x2{b1, b1};
+            if constexpr (EXQ) {
+                const float sc = h2f((uint16_t)(sz & 0xFFFFu));
+                const float s_new = sc == 0.f ? 0x1p-64f : sc;
+                ratio[j] = s_unit[j] * __builtin_amdgcn_rcpf(s_new);   // within 1 ulp
+                s_unit[j] = s_new;
+            } else {
+                const _Float16 sc = __builtin_bit_cast(_Float16, (uint16_t)(sz & 0xFFFFu));
+                qs2[j] = f16x2{sc, sc};
+            }
+        }
+    };
+    // memory phase of slice s: its activation fragments and (packed) weight fragments
+    u32x2 w8[4];
+    uint32_t w4[4];
+    auto read = [&](int s, int u) {
+        const int q = s / T::SPB;
+        const char* sA = sAr + (s & 3) * T::A_SLOT;
+        const char* sB = sBr + bslot(q);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const char* p = sB + col_rb(j) * 1024;
+            if constexpr (WF == W_BF16) bop[j] = *(const u32x4*)p;
+            else if constexpr (WF == W_INT8) w8[j] = *(const u32x2*)(p + 512 * (u & 1));
+            else w4[j] = *(const uint32_t*)(p + 256 * u);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) af[i] = *(const u32x4*)(sA + i * 16 * 64);
+        if (WF == W_INT4 && u == 0) regroup(q);
+    };
+    // the fragment of column tile j in the MFMA's format
+    auto unpack = [&](int j, int u) {
+        if constexpr (WF == W_INT8) {
+            const u32x2 c0 = i8x4_to_f16x4(w8[j].x), c1 = i8x4_to_f16x4(w8[j].y);
+            bop[j] = u32x4{c0.x, c0.y, c1.x, c1.y};
+        }
+        if constexpr (WF == W_INT4) {
+            bop[j] = i4x8_to_f16x8_q(w4[j], qbias[j], qbias64[j]);
+            if constexpr (!EXQ) {
+                const u32x4 d = bop[j];
+                bop[j] = u32x4{mul_h2(d.x, qs2[j]), mul_h2(d.y, qs2[j]), mul_h2(d.z, qs2[j]), mul_h2(d.w, qs2[j])};
+            } else if (u == 0) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i][j] *= ratio[j];
+            }
+        }
+    };
+    // compute phase.  Quantised weights go column by column, the next column's fragment
+    // unpacked (and, for the exact scheme, its accumulators rescaled) between the MFMAs of
+    // the current one: in the memory phase the same arithmetic delays the reads that the
+    // other wave of the SIMD waits for at the barrier (int4 131072 x 7168 x 8192: 12.07 ms
+    // there, 11.18 here; 12.30 in the kernel this replaced)
+    auto mfmas = [&](int u) {
+        if constexpr (WF == W_BF16) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    const int j = (i & 1) ? 3 - jj : jj;
+                    acc[i][j] = mfma16<AF>(af[i], bop[j], acc[i][j]);
+                }
+        } else {
+            #pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (j < 3) unpack(j + 1, u);
+#pragma unroll
+                for (int ii = 0; ii < 8; ++ii) {
+                    const int i = (j & 1) ? 7 - ii : ii;
+                    acc[i][j] = mfma16<AF>(af[i], bop[j], acc[i][j]);
+                }
+                if (!EXQ && j < 3) {
+#pragma unroll
+                    for (int t = 0; t < 8; ++t) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
+                        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);   // one unpacking step
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    auto barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto slice = [&](int s, auto uc) {
+        constexpr int u = decltype(uc)::value;
+        read(s, u);
+        issue(s, u);
+        unpack(0, u);
+        // the copies of slices s - 1 and s (int4: 4, 3, 2, 2 for u = 0 .. 3)
+        constexpr int NW = WF == W_BF16 ? 8 : WF == W_INT8 ? 6 : (u == 0 ? 6 : u == 1 ? 7 : u == 2 ? 5 : 4);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NW) : "memory");
+        barrier();
+        __builtin_amdgcn_s_setprio(1);
+        mfmas(u);
+        __builtin_amdgcn_s_setprio(0);
+        barrier();
+    };
+
+    // slices 0 .. 2 and the weights that the loop does not copy itself
+    copy_a(0);
+    copy_a(1);
+    copy_a(2);
+    constexpr int PRE = WF == W_BF16 ? 3 : WF == W_INT8 ? 2 : 1;
+#pragma unroll
+    for (int q = 0; q < PRE; ++q) {
+        copy_b(q, 0);
+        copy_b(q, 1);
+    }
+    if constexpr (WF == W_INT4) copy_sz(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    barrier();
+    if (wm) barrier();                               // the lower half runs one phase behind
+    int s = 0;
+    for (; s + 4 <= ns; s += 4) {
+        slice(s, std::integral_constant<int, 0>{});
+        slice(s + 1, std::integral_constant<int, 1>{});
+        slice(s + 2, std::integral_constant<int, 2>{});
+        slice(s + 3, std::integral_constant<int, 3>{});
+    }
+    if (WF != W_INT4 && s < ns) {
+        slice(s, std::integral_constant<int, 0>{});
+        slice(s + 1, std::integral_constant<int, 1>{});
+    }
+    if (!wm) barrier();                              // every wave has met the same number of barriers
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the epilogue reuses the rings
+    __syncthreads();
+
+    // ---- epilogue: element e of acc[i][j] of lane (r, g) is row 16 i + 4 g + e of the wave's
+    // tile, column r of row-block col_rb(j)
+    auto col_scale = [&](int j, int n, bool ok) {
+        float v = 1.f;
+        if constexpr (WF == W_INT8) v = ok ? h2f(a.scales[n]) : 0.f;
+        if constexpr (WF == W_INT4) v = s_unit[j];
+        return v;
+    };
+    if constexpr (EPI == EPI_PART || EPI == EPI_F32) {
         const int ncols = DUAL ? 2 * a.F : a.N;
-        float* out = a.out32 + (int64_t)blockIdx.y * a.M * ncols;
+        float* out = a.out32 + (EPI == EPI_PART ? (int64_t)blockIdx.y * a.M * ncols : 0);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            int n;
-            if constexpr (DUAL) n = (j == 0 ? 0 : a.F) + nt * 128 + wn * 32 + l32;
-            else n = nt * 256 + wn * 64 + 32 * j + l32;
-            if (DUAL ? nt * 128 + wn * 32 + l32 >= a.F : n >= a.N) continue;
-            float sn = 1.f;
-            if constexpr (WF == W_INT8) sn = h2f(a.scales[n]);
-            if constexpr (WF == W_INT4) sn = s_unit[j];
+        for (int j = 0; j < 4; ++j) {
+            bool v;
+            const int n = grow_block(col_rb(j), v) * 16 + r;
+            if (!v) continue;
+            const float sn = col_scale(j, n, true);
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 8; ++i)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = m0 + wm * 128 + 32 * i + 8 * (e >> 2) + 4 * h32 + (e & 3);
+                for (int e = 0; e < 4; ++e) {
+                    const int m = m0 + wm * 128 + 16 * i + 4 * g + e;
                     if (m < a.M) out[(int64_t)m * ncols + n] = acc[i][j][e] * sn;
                 }
         }
     } else if constexpr (DUAL) {
         // SwiGLU: a = act(bf16(silu(gate) * up)) per (m, f); the tile's 256 x 128 outputs are
-        // staged in LDS (the stage buffers are free now) and written as 16-byte pieces of
-        // whole 256-byte rows
+        // staged in LDS (the rings are free now) and written as 16-byte pieces of whole
+        // 256-byte rows
         constexpr int FS = 136;                               // LDS row stride (u16)
         static_assert(256 * FS * 2 <= T::SMEM, "SwiGLU staging fits the LDS");
         uint16_t* st16 = (uint16_t*)smem;
-        const int fl = wn * 32 + l32;                         // the lane's column in the tile
-        const int f = nt * 128 + fl;
-        float sg = 1.f, su = 1.f;
-        if constexpr (WF == W_INT8) {
-            if (f < a.F) {
-                sg = h2f(a.scales[f]);
-                su = h2f(a.scales[a.F + f]);
-            }
-        }
-        if constexpr (WF == W_INT4) {
-            sg = s_unit[0];
-            su = s_unit[1];
-        }
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 2; ++j) {
+            const int fl = (wn * 2 + j) * 16 + r, f = nt * 128 + fl;    // the lane's column in the tile
+            const float sg = col_scale(j, f, f < a.F), su = col_scale(j + 2, a.F + f, f < a.F);
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int row = wm * 128 + 32 * i + 8 * (e >> 2) + 4 * h32 + (e & 3);
-                const float gv = acc[i][0][e] * sg, uv = acc[i][1][e] * su;
-                st16[row * FS + fl] = act_store(bfround(silu_f(gv) * uv), a.out_fmt);
-            }
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int row = wm * 128 + 16 * i + 4 * g + e;
+                    const float gv = acc[i][j][e] * sg, uv = acc[i][j + 2][e] * su;
+                    st16[row * FS + fl] = act_store(bfround(silu_f(gv) * uv), a.out_fmt);
+                }
+        }
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < 8; ++t) {                         // 256 rows x 16 pieces of 8 columns
@@ -708,37 +748,18 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
             if (m < a.M && f0 < a.F)
                 *(u32x4*)(a.out16 + (int64_t)m * a.F + f0) = *(const u32x4*)(st16 + row * FS + c);
         }
-    } else if constexpr (EPI == EPI_F32) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = nt * 256 + wn * 64 + 32 * j + l32;
-            if (n >= a.N) continue;
-            float sn = 1.f;
-            if constexpr (WF == W_INT8) sn = h2f(a.scales[n]);
-            if constexpr (WF == W_INT4) sn = s_unit[j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int m = m0 + wm * 128 + 32 * i + 8 * (e >> 2) + 4 * h32 + (e & 3);
-                    if (m < a.M) a.out32[(int64_t)m * a.N + n] = acc[i][j][e] * sn;
-                }
-        }
     } else {
         // residual: out = bf16(resid + acc).  Each wave stages its 128 x 64 results in two
         // passes of 64 rows through its own LDS region (fp32), then reads 8 consecutive
         // columns per lane and writes them, with the matching resid piece, as 16-byte
         // pieces of 128-byte row segments; a pass's resid loads go out first.
-        constexpr int ES = 72;                                // LDS row stride (floats): rows r, r + 4 are 32 banks apart
-        static_assert(8 * 64 * ES * 4 <= T::SMEM, "residual staging fits the LDS");
+        constexpr int ES = T::ES;                             // rows 4 apart are 16 banks apart
         float* reg = (float*)smem + w * 64 * ES;
-        float sn[2];
+        float sn[4];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = nt * 256 + wn * 64 + 32 * j + l32;
-            sn[j] = 1.f;
-            if constexpr (WF == W_INT8) sn[j] = n < a.N ? h2f(a.scales[n]) : 0.f;
-            if constexpr (WF == W_INT4) sn[j] = s_unit[j];
+        for (int j = 0; j < 4; ++j) {
+            const int n = nt * 256 + wn * 64 + 16 * j + r;
+            sn[j] = col_scale(j, n, n < a.N);
         }
         const int rl = lane >> 3, c8 = (lane & 7) * 8;        // 8 rows x 8 pieces per instruction
         const int n8 = nt * 256 + wn * 64 + c8;
@@ -752,20 +773,18 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
                 if (m < a.M && n8 < a.N) rv[t] = *(const u32x4*)(a.resid + (int64_t)m * a.N + n8);
             }
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
+            for (int ii = 0; ii < 4; ++ii)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < 4; ++j)
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int row = 32 * ii + 8 * (e >> 2) + 4 * h32 + (e & 3);
-                        reg[row * ES + 32 * j + l32] = acc[2 * p + ii][j][e] * sn[j];
-                    }
-            __syncthreads();
+                    for (int e = 0; e < 4; ++e) reg[(16 * ii + 4 * g + e) * ES + 16 * j + r] = acc[4 * p + ii][j][e] * sn[j];
+            // the region is the wave's own: its LDS operations complete in order, no barrier
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
             for (int t = 0; t < 8; ++t) {
                 const int row = 8 * t + rl, m = m0 + wm * 128 + 64 * p + row;
-                if (m >= a.M || n8 >= a.N) continue;
                 const f32x4 v0 = *(const f32x4*)(reg + row * ES + c8), v1 = *(const f32x4*)(reg + row * ES + c8 + 4);
+                if (m >= a.M || n8 >= a.N) continue;
                 const uint32_t r4[4] = {rv[t].x, rv[t].y, rv[t].z, rv[t].w};
                 const float vv[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
                 uint32_t o[4];
@@ -775,7 +794,7 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
                            ((uint32_t)f2bf(bf2f(r4[q] >> 16) + vv[2 * q + 1]) << 16);
                 *(u32x4*)(a.out16 + (int64_t)m * a.N + n8) = u32x4{o[0], o[1], o[2], o[3]};
             }
-            __syncthreads();                                  // before the next pass overwrites the region
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
     }
 }

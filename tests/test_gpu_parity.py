@@ -435,3 +435,26 @@ def test_prefill_attention_repeat_path(case, monkeypatch):
     assert res.prefill_err <= TOL
     assert all(e <= TOL for e in res.layer_errs)
     assert max(res.decode_errs) <= TOL
+
+
+# Edges of the large prefill tiling (256 x 256 tiles, K in 32-k slices four to a loop turn):
+# an odd number of 64-input stages (the loop's two-slice tail; hidden = 17 x 64, and split-K
+# ranges of 6 and 5 stages for o and down), the shortest K of each format (one 64-input
+# stage, one 128-input group) and a ragged last row tile (M = 5 x 817).
+EDGE_CASES = [
+    ("edge-bf16-odd-stages", Shape(1, 1088, 17, 17, 64, 1088, 5, 817, 819), "bf16", "bf16", 5, 817, 1, (0, 4)),
+    ("edge-int8-odd-stages", Shape(1, 1088, 17, 17, 64, 1088, 5, 817, 819), "int8", "bf16", 5, 817, 1, (0, 4)),
+    ("edge-bf16-one-stage", Shape(1, 64, 1, 1, 64, 2048, 5, 817, 819), "bf16", "bf16", 5, 817, 1, (4,)),
+    ("edge-int8-one-stage", Shape(1, 64, 1, 1, 64, 2048, 5, 817, 819), "int8", "int8", 5, 817, 1, (4,)),
+    ("edge-int4-one-group", Shape(1, 128, 1, 1, 128, 2048, 5, 817, 819), "int4", "bf16", 5, 817, 1, (4,)),
+]
+
+
+@pytest.mark.parametrize("case", EDGE_CASES, ids=[c[0] for c in EDGE_CASES])
+def test_parity_large_tile_edges(case):
+    name, shape, wq, kvq, B, P, S, rows = case
+    log(f"case {name}: {shape} {wq}/{kvq} B={B} P={P} S={S} rows={rows}")
+    res = run_parity(shape, wq, kvq, B, P, S, rows=rows)
+    _report(name, res)
+    assert res.prefill_err <= TOL
+    assert max(res.decode_errs) <= TOL
