@@ -458,3 +458,14 @@ def test_parity_large_tile_edges(case):
     _report(name, res)
     assert res.prefill_err <= TOL
     assert max(res.decode_errs) <= TOL
+
+
+@pytest.mark.parametrize("B", [2, 16, 17, 33, 64])
+def test_sp24_decode_batches(B):
+    """The 2:4 decode projection stages exactly B activation rows: one and two 32-token tiles,
+    whole and ragged, with k-ranges of several staging batches (hidden 1152, ffn 2176)."""
+    log(f"sp24 decode B={B}")
+    rows = sorted({0, B // 2, B - 1})
+    res = run_parity(Shape(1, 1152, 9, 9, 128, 2176, B, 6, 8), "sp24", "bf16", B, 6, 2, rows=rows)
+    assert res.prefill_err <= TOL
+    assert max(res.decode_errs) <= TOL
