@@ -469,3 +469,13 @@ def test_sp24_decode_batches(B):
     res = run_parity(Shape(1, 1152, 9, 9, 128, 2176, B, 6, 8), "sp24", "bf16", B, 6, 2, rows=rows)
     assert res.prefill_err <= TOL
     assert max(res.decode_errs) <= TOL
+
+
+# Decode attention without a merge kernel (a batch whose context is at most 16 blocks of 32
+# keys) and with one (17 blocks), grouped queries, at the last position of the cache.
+@pytest.mark.parametrize("seq", [33, 512, 513])
+def test_decode_attention_one_workgroup_edge(seq):
+    log(f"decode attention, cache of {seq} positions")
+    res = run_parity(Shape(1, 256, 4, 2, 64, 384, 3, seq - 2, seq), "bf16", "int8", 3, seq - 2, 2)
+    assert res.prefill_err <= TOL
+    assert max(res.decode_errs) <= TOL
