@@ -508,7 +508,7 @@ fp_status run_skinny_batch(fp_layer* h, const uint16_t* X, const Mat& m, int M, 
 }
 
 fp_status run_gemm(fp_layer* h, const uint16_t* X, const Mat& m, int M, int epi, float* out32,
-                   uint16_t* out16, const uint16_t* resid, hipStream_t st) {
+                   uint16_t* out16, const uint16_t* resid, hipStream_t st, const RopeKvArgs* ro = nullptr) {
     if (m.wf == W_SP24) {
         Sp24Args a{};
         a.X = X;
@@ -541,7 +541,8 @@ fp_status run_gemm(fp_layer* h, const uint16_t* X, const Mat& m, int M, int epi,
     a.out16 = out16;
     a.resid = resid;
     a.out_fmt = h->act_fmt;
-    HIPCHK(launch_gemm(a, h->wq, epi, st));
+    if (epi == EPI_ROPE) HIPCHK(launch_gemm_rope(a, *ro, h->wq, st));
+    else HIPCHK(launch_gemm(a, h->wq, epi, st));
     return FP_OK;
 }
 
@@ -623,9 +624,15 @@ fp_status enqueue_prefill(fp_layer* h, const uint16_t* x, int B, int P, uint16_t
         }
         normed = false;
         h->prof.mark(FP_K_QKV, l);
-        if ((rc = run_gemm(h, h->act_in, W.qkv, M, EPI_F32, h->qkv32, nullptr, nullptr, st))) return rc;
-        h->prof.mark(FP_K_ROPE_KV, l);
-        HIPCHK(launch_rope_kv(rope_args(h, l, h->qkv32, 1, M, P, nullptr, dump), st));
+        const RopeKvArgs ro = rope_args(h, l, h->qkv32, 1, M, P, nullptr, dump);
+        if (!dump && gemm_rope_supported(M, W.qkv.N, W.qkv.K, P, s.head_dim, W.qkv.wf)) {
+            // rotary embedding and KV append in the projection's epilogue
+            if ((rc = run_gemm(h, h->act_in, W.qkv, M, EPI_ROPE, nullptr, nullptr, nullptr, st, &ro))) return rc;
+        } else {
+            if ((rc = run_gemm(h, h->act_in, W.qkv, M, EPI_F32, h->qkv32, nullptr, nullptr, st))) return rc;
+            h->prof.mark(FP_K_ROPE_KV, l);
+            HIPCHK(launch_rope_kv(ro, st));
+        }
         AttnPreArgs aa{};
         aa.q = h->q16;
         aa.kc = h->kc[l];

@@ -33,7 +33,9 @@ extern thread_local LaunchTimer g_launch_timer;
 enum WFmt { W_BF16 = 0, W_INT8 = 1, W_INT4 = 2, W_SP24 = 3 };
 // EPI_PART: fp32 partial sums of one k-split, [ks, M, N] (or [ks, M, 2F] for the
 // [gate; up] matrix), multiplied by the int8 row scales; a reduction kernel finishes.
-enum Epi { EPI_F32 = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_PART = 3 };
+// EPI_ROPE: the qkv projection of a prompt of whole 32-position blocks on the large tiling;
+// rotated queries, keys and values go straight to q and the cache (launch_gemm_rope).
+enum Epi { EPI_F32 = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_PART = 3, EPI_ROPE = 4 };
 // Activation format of a GEMM's A operand: bf16 for bf16 weights, fp16 for quantised
 // weights (the fp16 copy of a bf16-rounded value is exact in fp16's normal range).
 enum ActFmt { ACT_BF16 = 0, ACT_F16 = 1 };
@@ -207,6 +209,10 @@ int skinny_batch_tiles(int N, int dual_F, int wf);
 int skinny_batch_chunk();
 hipError_t launch_skinny_batch(const SkinnyArgs& a, int wf, int ks, hipStream_t st);
 hipError_t launch_gemm(const GemmArgs& a, int wf, int epi, hipStream_t st);
+// The qkv projection with the rotary embedding and the KV append in its epilogue: writes
+// what launch_gemm (EPI_F32) and launch_rope_kv write, bit for bit, without the fp32 q, k, v.
+bool gemm_rope_supported(int M, int N, int K, int T, int d, int wf);
+hipError_t launch_gemm_rope(const GemmArgs& a, const RopeKvArgs& ro, int wf, hipStream_t st);
 // Split-K on the large tiling for prefill GEMMs with too few 256 x 256 tiles to fill
 // the GPU: the split factor (1: no split) and k per split for an [M, N] x [N, K]
 // product (dual_F > 0: the [gate; up] matrix), and the launch writing EPI_PART partials.

@@ -425,8 +425,151 @@ __device__ __forceinline__ u32x4 i4x8_to_f16x8_q(uint32_t w, f16x2 b1024, f16x2 
     return r;
 }
 
+// ---- EPI_ROPE: the rotary embedding and the KV append on one staged half of a tile.
+// st: 128 rows x 256 columns of q | k | v (fp32, row stride ROPE_RS) = 256 / D whole heads of
+// 128 tokens m .. m + 127, all in whole 32-position blocks; scl: 128 x 4 floats.  The
+// arithmetic and the rounding are those of rope_q_kernel and kv_append_kernel (rows.hip).
+constexpr int ROPE_RS = 260;      // floats: the accumulators' rows 4 apart are 16 banks apart
+// fp16 queries: product, fused second product and the rounding to fp16 in two instructions
+// (outside the contract(off) region, like the same expression in rope_q_kernel)
+__device__ __forceinline__ void rot_f16x4(const f32x4& u, const f32x4& v, const f32x4& c, const f32x4& s, u32x2& lo, u32x2& hi) {
+    f32x4 a, b;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        a[e] = __fsub_rn(__fmul_rn(u[e], c[e]), __fmul_rn(v[e], s[e]));
+        b[e] = __fadd_rn(__fmul_rn(v[e], c[e]), __fmul_rn(u[e], s[e]));
+    }
+    lo = u32x2{pack_f16_hw(a[0], a[1]), pack_f16_hw(a[2], a[3])};
+    hi = u32x2{pack_f16_hw(b[0], b[1]), pack_f16_hw(b[2], b[3])};
+}
+#pragma clang fp contract(off)
+template <int D>
+__device__ __forceinline__ void rope_store(const RopeKvArgs& ro, const float* st, float* scl, int m, int head0) {
+    constexpr int HALF = D / 2, HPT = 256 / D, LPR = D / 8, RPP = 512 / LPR;   // lanes per row, rows per pass
+    const int tid = threadIdx.x;
+    const int l = tid % LPR;
+    auto q8 = [](float v, float s) -> uint32_t {
+        if (s == 0.f) return 0u;
+        return (uint32_t)(uint8_t)(int8_t)(int)fminf(fmaxf(rintf(__fdiv_rn(v, s)), -127.f), 127.f);
+    };
+    auto row_max = [](float v) {
+#pragma unroll
+        for (int o = LPR / 2; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+        return v;
+    };
+    auto pack4 = [](const f32x4& v) {
+        return u32x2{(uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16), (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16)};
+    };
+#pragma unroll 1
+    for (int ps = 0; ps < 128 / RPP; ++ps) {
+        const int row = tid / LPR + ps * RPP, tok = m + row;
+        const bool ok = tok < ro.M;
+        const int b = ok ? tok / ro.T : 0, pos = ok ? tok - b * ro.T : 0;
+        const f32x4 c = *(const f32x4*)(ro.cos_t + (int64_t)pos * HALF + 4 * l);
+        const f32x4 s = *(const f32x4*)(ro.sin_t + (int64_t)pos * HALF + 4 * l);
+#pragma unroll 1
+        for (int hh = 0; hh < HPT; ++hh) {
+            const int h = head0 + hh;                       // q heads, then k heads, then v heads
+            if (h >= ro.nh + 2 * ro.nkv) break;
+            const f32x4 u = *(const f32x4*)(st + row * ROPE_RS + hh * D + 4 * l);
+            const f32x4 v = *(const f32x4*)(st + row * ROPE_RS + hh * D + HALF + 4 * l);
+            // as those kernels' arithmetic is compiled: one product rounded, the other fused
+            f32x4 lo, hi;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                lo[e] = fmaf(u[e], c[e], -(v[e] * s[e]));
+                hi[e] = fmaf(v[e], c[e], u[e] * s[e]);
+            }
+            if (h < ro.nh) {
+                uint16_t* q = ro.qout + (((int64_t)b * ro.nh + h) * ro.T + pos) * D + 4 * l;
+                u32x2 ql = u32x2{pack_bf16_hw(lo[0], lo[1]), pack_bf16_hw(lo[2], lo[3])};
+                u32x2 qh = u32x2{pack_bf16_hw(hi[0], hi[1]), pack_bf16_hw(hi[2], hi[3])};
+                if (ro.kv_int8) rot_f16x4(u, v, c, s, ql, qh);
+                if (ok) {
+                    *(u32x2*)q = ql;
+                    *(u32x2*)(q + HALF) = qh;
+                }
+            } else if (h < ro.nh + ro.nkv) {
+                const int64_t crow = ((int64_t)b * ro.nkv + (h - ro.nh)) * ro.kv_stride + pos;
+                if (!ro.kv_int8) {
+                    uint16_t* kd = (uint16_t*)ro.kc + crow * D + 4 * l;
+                    if (ok) {
+                        *(u32x2*)kd = pack4(lo);
+                        *(u32x2*)(kd + HALF) = pack4(hi);
+                    }
+                } else {
+                    float t = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t = fmaxf(t, fmaxf(fabsf(lo[e]), fabsf(hi[e])));
+                    const uint16_t sh = f2h(__fdiv_rn(row_max(t), 127.0f));
+                    const float sf = h2f(sh);
+                    if (ok) {
+                        int8_t* kd = (int8_t*)ro.kc + crow * D + 4 * l;
+                        *(uint32_t*)kd = q8(lo[0], sf) | (q8(lo[1], sf) << 8) | (q8(lo[2], sf) << 16) | (q8(lo[3], sf) << 24);
+                        *(uint32_t*)(kd + HALF) = q8(hi[0], sf) | (q8(hi[1], sf) << 8) | (q8(hi[2], sf) << 16) | (q8(hi[3], sf) << 24);
+                        if (l == 0) ro.ks_out[crow] = sh;
+                    }
+                }
+            } else if (ro.kv_int8) {                        // the value rows' scales
+                float t = 0.f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t = fmaxf(t, fmaxf(fabsf(u[e]), fabsf(v[e])));
+                const uint16_t sh = f2h(__fdiv_rn(row_max(t), 127.0f));
+                if (l == 0) {
+                    scl[row * 4 + hh] = h2f(sh);
+                    if (ok) ro.vs_out[((int64_t)b * ro.nkv + (h - ro.nh - ro.nkv)) * ro.kv_stride + pos] = sh;
+                }
+            }
+        }
+    }
+    if (head0 + HPT <= ro.nh + ro.nkv) return;              // no value head in the tile (uniform)
+    __syncthreads();                                        // the scales
+    // values: transposed 32-position blocks; slots 8 o .. 8 o + 3 hold positions 4 o .. 4 o + 3
+    // and slots 8 o + 4 .. 8 o + 7 positions 16 + 4 o .. 16 + 4 o + 3
+#pragma unroll 1
+    for (int hh = 0; hh < HPT; ++hh) {
+        const int vh = head0 + hh - ro.nh - ro.nkv;
+        if (vh < 0) continue;
+        if (vh >= ro.nkv) break;
+#pragma unroll 1
+        for (int blk = 0; blk < 4; ++blk) {
+            const int tok = m + 32 * blk;
+            if (tok >= ro.M) break;
+            const int b = tok / ro.T, pos = tok - b * ro.T;
+            const int64_t vb = (((int64_t)b * ro.nkv + vh) * ro.nblk + pos / VT_BLK) * D * VT_BLK;
+            const float* col = st + 32 * blk * ROPE_RS + hh * D;
+            if (!ro.kv_int8) {
+                for (int it = tid; it < D * 4; it += 512) {
+                    const int dim = it >> 2, o = it & 3;
+                    f32x4 x0, x1;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        x0[e] = col[(4 * o + e) * ROPE_RS + dim];
+                        x1[e] = col[(16 + 4 * o + e) * ROPE_RS + dim];
+                    }
+                    const u32x2 p0 = pack4(x0), p1 = pack4(x1);
+                    *(u32x4*)((uint16_t*)ro.vc + vb + dim * VT_BLK + 8 * o) = u32x4{p0.x, p0.y, p1.x, p1.y};
+                }
+            } else {
+                for (int it = tid; it < D * 4; it += 512) {
+                    const int dim = it >> 2, o = it & 3;
+                    uint32_t w0 = 0, w1 = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r0 = 4 * o + e, r1 = 16 + 4 * o + e;
+                        w0 |= q8(col[r0 * ROPE_RS + dim], scl[(32 * blk + r0) * 4 + hh]) << (8 * e);
+                        w1 |= q8(col[r1 * ROPE_RS + dim], scl[(32 * blk + r1) * 4 + hh]) << (8 * e);
+                    }
+                    *(u32x2*)((int8_t*)ro.vc + vb + dim * VT_BLK + 8 * o) = u32x2{w0, w1};
+                }
+            }
+        }
+    }
+}
+#pragma clang fp contract(on)
+
 template <int WF, int EPI, bool DUAL>
-__global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
+__global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a, RopeKvArgs ro) {
     using T = BigT<WF>;
     constexpr int AF = (WF == W_BF16) ? ACT_BF16 : ACT_F16;
     static_assert(DUAL == (EPI == EPI_SWIGLU) || EPI == EPI_PART, "dual tiling");
@@ -469,7 +612,7 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
         if constexpr (DUAL) return j < 2 ? wn * 2 + j : 8 + wn * 2 + (j - 2);
         else return wn * 4 + j;
     };
-    constexpr bool EXQ = WF == W_INT4 && (!GEMM_FASTQ || EPI == EPI_F32);   // int4: exact scheme (qkv)
+    constexpr bool EXQ = WF == W_INT4 && (!GEMM_FASTQ || EPI == EPI_F32 || EPI == EPI_ROPE);   // int4: exact scheme (qkv)
 
     // ---- copies.  Rows past M and blocks past the matrix read past the end of their buffer
     // resource and land as zeros, and so do slices past the k-range (resource size 0), so every
@@ -720,6 +863,33 @@ __global__ void __launch_bounds__(512, 1) gemm_big_kernel(GemmArgs a) {
                     if (m < a.M) out[(int64_t)m * ncols + n] = acc[i][j][e] * sn;
                 }
         }
+    } else if constexpr (EPI == EPI_ROPE) {
+        // rotary embedding and KV append: the tile's upper and lower 128 rows in turn through
+        // LDS.  Bound by its stores; in place of an fp32 store here (2 GB for a 32768-token 13B
+        // prompt batch) and two kernels that read it back.
+        static_assert((128 * ROPE_RS + 512) * 4 <= T::SMEM, "staging fits the LDS");
+        float* stg = (float*)smem;
+        float* scl = stg + 128 * ROPE_RS;
+#pragma unroll 1
+        for (int p = 0; p < 2; ++p) {
+            if (m0 + 128 * p >= a.M) break;                   // uniform
+            if (wm == p) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int n = nt * 256 + wn * 64 + 16 * j + r;
+                    const float sn = col_scale(j, n, n < a.N);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            stg[(16 * i + 4 * g + e) * ROPE_RS + wn * 64 + 16 * j + r] = acc[i][j][e] * sn;
+                }
+            }
+            __syncthreads();
+            if (ro.d == 128) rope_store<128>(ro, stg, scl, m0 + 128 * p, nt * 2);
+            else rope_store<64>(ro, stg, scl, m0 + 128 * p, nt * 4);
+            __syncthreads();
+        }
     } else if constexpr (DUAL) {
         // SwiGLU: a = act(bf16(silu(gate) * up)) per (m, f); the tile's 256 x 128 outputs are
         // staged in LDS (the rings are free now) and written as 16-byte pieces of whole
@@ -806,9 +976,9 @@ static hipError_t launch_big(const GemmArgs& a, int epi, hipStream_t st) {
     b.tiles_m = (a.M + BT - 1) / BT;
     dim3 grid(b.tiles_n * b.tiles_m);
     switch (epi) {
-        case EPI_F32: FP_LAUNCH((gemm_big_kernel<WF, EPI_F32, false>), grid, dim3(512), 0, st, b); break;
-        case EPI_RESID: FP_LAUNCH((gemm_big_kernel<WF, EPI_RESID, false>), grid, dim3(512), 0, st, b); break;
-        case EPI_SWIGLU: FP_LAUNCH((gemm_big_kernel<WF, EPI_SWIGLU, true>), grid, dim3(512), 0, st, b); break;
+        case EPI_F32: FP_LAUNCH((gemm_big_kernel<WF, EPI_F32, false>), grid, dim3(512), 0, st, b, RopeKvArgs{}); break;
+        case EPI_RESID: FP_LAUNCH((gemm_big_kernel<WF, EPI_RESID, false>), grid, dim3(512), 0, st, b, RopeKvArgs{}); break;
+        case EPI_SWIGLU: FP_LAUNCH((gemm_big_kernel<WF, EPI_SWIGLU, true>), grid, dim3(512), 0, st, b, RopeKvArgs{}); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -820,8 +990,8 @@ static hipError_t launch_big_split(const GemmArgs& a, bool dual, int ks, hipStre
     b.tiles_n = dual ? (a.F + 127) / 128 : (a.N + BT - 1) / BT;
     b.tiles_m = (a.M + BT - 1) / BT;
     dim3 grid(b.tiles_n * b.tiles_m, ks);
-    if (dual) FP_LAUNCH((gemm_big_kernel<WF, EPI_PART, true>), grid, dim3(512), 0, st, b);
-    else FP_LAUNCH((gemm_big_kernel<WF, EPI_PART, false>), grid, dim3(512), 0, st, b);
+    if (dual) FP_LAUNCH((gemm_big_kernel<WF, EPI_PART, true>), grid, dim3(512), 0, st, b, RopeKvArgs{});
+    else FP_LAUNCH((gemm_big_kernel<WF, EPI_PART, false>), grid, dim3(512), 0, st, b, RopeKvArgs{});
     return hipGetLastError();
 }
 
@@ -864,6 +1034,38 @@ hipError_t launch_gemm_big(const GemmArgs& a, int wf, int epi, hipStream_t st) {
         case W_BF16: return launch_big<W_BF16>(a, epi, st);
         case W_INT8: return launch_big<W_INT8>(a, epi, st);
         case W_INT4: return launch_big<W_INT4>(a, epi, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// Where the large tiling runs: enough 256 x 256 tiles, K in whole stages.
+static bool use_big(int M, int N, int K, int wf) {
+    return ((M + BT - 1) / BT) * ((N + BT - 1) / BT) >= GEMM_BIG_MIN_TILES && K % big_tk(wf) == 0;
+}
+
+// Prompts of whole 32-position blocks only: a row group of 32 is then one value block of one
+// sequence, written whole; other prompts (and the debug dump) keep the separate kernels.
+bool gemm_rope_supported(int M, int N, int K, int T, int d, int wf) {
+    return (wf == W_BF16 || wf == W_INT8 || wf == W_INT4) && (d == 64 || d == 128) && T % VT_BLK == 0 && use_big(M, N, K, wf);
+}
+
+template <int WF>
+static hipError_t launch_rope_w(const GemmArgs& a, const RopeKvArgs& ro, hipStream_t st) {
+    GemmArgs b = a;
+    b.tiles_n = (a.N + BT - 1) / BT;
+    b.tiles_m = (a.M + BT - 1) / BT;
+    FP_LAUNCH((gemm_big_kernel<WF, EPI_ROPE, false>), dim3(b.tiles_n * b.tiles_m), dim3(512), 0, st, b, ro);
+    return hipGetLastError();
+}
+
+hipError_t launch_gemm_rope(const GemmArgs& a, const RopeKvArgs& ro, int wf, hipStream_t st) {
+    if (!gemm_rope_supported(a.M, a.N, a.K, ro.T, ro.d, wf) || ro.dump != nullptr || ro.M != a.M || a.M % ro.T != 0 ||
+        a.N != (ro.nh + 2 * ro.nkv) * ro.d || ro.nblk * VT_BLK < ro.T || ro.kv_stride < ro.nblk * VT_BLK)
+        return hipErrorInvalidValue;
+    switch (wf) {
+        case W_BF16: return launch_rope_w<W_BF16>(a, ro, st);
+        case W_INT8: return launch_rope_w<W_INT8>(a, ro, st);
+        case W_INT4: return launch_rope_w<W_INT4>(a, ro, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -479,3 +479,40 @@ def test_decode_attention_one_workgroup_edge(seq):
     res = run_parity(Shape(1, 256, 4, 2, 64, 384, 3, seq - 2, seq), "bf16", "int8", 3, seq - 2, 2)
     assert res.prefill_err <= TOL
     assert max(res.decode_errs) <= TOL
+
+
+# The qkv projection with the rotary embedding and KV append in its epilogue (large tiling,
+# prompts of whole 32-position blocks) against the separate kernels, which a debug dump
+# switches back to: outputs, cache codes and scales agree bit for bit.  Tiles that hold q and k,
+# k and v, and all three kinds of heads; a ragged last column tile and last row tile (M = 5 x
+# 832 = 16 x 256 + 64); every weight format with both caches.
+ROPE_CASES = [
+    ("int4-int8kv-d128", Shape(1, 1152, 9, 9, 128, 256, 5, 832, 832), "int4", "int8", 5, 832),
+    ("bf16-d128", Shape(1, 1152, 9, 9, 128, 256, 5, 832, 840), "bf16", "bf16", 5, 832),
+    ("int8-int8kv-d64-gqa3", Shape(1, 1152, 30, 10, 64, 256, 5, 832, 833), "int8", "int8", 5, 832),
+    ("int4-bf16kv-d64", Shape(1, 1152, 30, 3, 64, 256, 5, 832, 832), "int4", "bf16", 5, 832),
+    ("bf16-int8kv-two-blocks", Shape(1, 576, 32, 2, 64, 256, 64, 64, 64), "bf16", "int8", 64, 64),
+]
+
+
+@pytest.mark.parametrize("case", ROPE_CASES, ids=[c[0] for c in ROPE_CASES])
+def test_fused_rope_epilogue_bit_exact(case):
+    import torch
+    from paper_2501_13111_amd import Fingerprint, fill_normal
+    name, shape, wq, kvq, B, P = case
+    log(f"fused rope {name}")
+    nqkv = (shape.n_heads + 2 * shape.n_kv_heads) * shape.head_dim
+    assert -(-B * P // 256) * -(-nqkv // 256) >= 128          # the large tiling
+    outs = []
+    for dumped in (False, True):
+        with Fingerprint(shape, wq, kvq, seed=21) as fp:
+            dump = torch.empty(2 * B * P * shape.n_kv_heads * shape.head_dim, dtype=torch.float32, device="cuda")
+            fp.set_debug_kv_dump(dump if dumped else None)
+            x = torch.empty(B * P * shape.hidden, dtype=torch.bfloat16, device="cuda")
+            fill_normal(x, 21, -1, 15, 0.0, 1.0)
+            y = torch.empty_like(x)
+            fp.prefill(x, y, B, P)
+            torch.cuda.synchronize()
+            outs.append((bf16_to_np(y),) + fp.export_kv(0))
+    for a, b in zip(*outs):
+        assert (a is None and b is None) or np.array_equal(a, b)
