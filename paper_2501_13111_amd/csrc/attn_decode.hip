@@ -111,15 +111,15 @@ __device__ __forceinline__ int qdim(int j, int g) {
     else return 32 * j + 8 * g;
 }
 
-#ifndef ATTN_DEC_PD
-#define ATTN_DEC_PD 2
-#endif
 template <int D, bool KV8>
 struct DecChunk {
     static constexpr int NK = KV8 ? D / 64 : D / 32;   // 16-byte K loads per key tile
-    // chunks in flight per wave (measured: three or four in flight are no faster than
-    // two on the batched workloads, four slower)
-    static constexpr int PD = ATTN_DEC_PD;
+    // chunks in flight per wave.  bf16 caches: one, and three workgroups per CU instead of two (143
+    // registers instead of 187): their queries' and appends' round trips cover each other
+    // (13B step at 32 sequences of 144 positions 99.1 -> 95.7 us, of 1008 positions 211.8 ->
+    // 208.9).  int8 caches, whose chunks are half the bytes: two (7B int8 step 83.2 us, 87.1 with
+    // one); three or four are no faster.
+    static constexpr int PD = KV8 ? 2 : 1;
     u32x4 k[2][NK];
     typename std::conditional<KV8, u32x2, u32x4>::type v[D / 16];   // int8: 8 codes; bf16: 8 values
     u32x2 ks[2], vs[2];                                 // int8: fp16 scales of keys 16 t + 4 g + i
