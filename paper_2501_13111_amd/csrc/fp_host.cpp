@@ -1007,11 +1007,11 @@ fp_status alloc_storage(fp_layer* h) {
     if ((st = alloc_t(h, &h->part2, (size_t)KSMAX * s.max_batch * 2 * F, &h->bytes_ws))) return st;
     {
         // the largest split-K partial buffer any prefill size up to Mmax asks for (the split
-        // factor depends on the number of 256-row tiles, so the worst case is at a whole tile)
+        // factor depends on the number of 256-row tiles, so the worst case is at a whole tile;
+        // below one tile also on the rows)
         size_t pp = 0;
         const int Mp = (int)act_elems(h);
-        for (int tm = 1; (int64_t)(tm - 1) * 256 < Mp; ++tm) {
-            const int M = std::min(tm * 256, Mp);
+        for (int M = std::min(2, Mp); M > 0; M = M == Mp ? 0 : M < 256 ? M + 1 : std::min(M + 256, Mp)) {
             int kr;
             const int ko = prefill_split(h, M, H, h->q_dim, 0, &kr);
             const int kg = prefill_split(h, M, 2 * F, H, F, &kr);

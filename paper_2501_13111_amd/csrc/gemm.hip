@@ -1005,13 +1005,25 @@ int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange) {
     const int tk = big_tk(wf);
     const int stages = (K + tk - 1) / tk;
     *krange = stages * tk;
-    if (M < BT || tiles >= 256 || K % tk != 0) return 1;
+    if (M < 2 || tiles >= 256 || K % tk != 0) return 1;
     // one round of workgroups (one per compute unit), at least four stages per split
     int ks = 256 / tiles;
     if (ks > GEMM_SPLIT_MAX) ks = GEMM_SPLIT_MAX;
     if (ks > stages / 4) ks = stages / 4;
     if (ks < 2) return 1;
     const int per = (stages + ks - 1) / ks;
+    if (M < BT) {
+        // Less than one row tile: the small tiling walks K on few workgroups (0.57 us per 64
+        // inputs, and the residual GEMMs need an RMSNorm launch after it), the split one pays a
+        // reduction and its partials' traffic.  In us, fitted to 8 to 255 rows of K 1024 to
+        // 11008: e.g. 100 rows, int4 4096 x 11008 102 -> 31 (with the norm), 7168 x 8192 SwiGLU
+        // 74 -> 32; but 22016 x 4096 SwiGLU on 172 workgroups either way 39 -> 43 at 8 rows.
+        const int ncols = dual_F > 0 ? 2 * dual_F : N;
+        const int small = ((M + 63) / 64) * (dual_F > 0 ? (dual_F + 63) / 64 : (N + GBN - 1) / GBN);
+        const double t_small = 3.0 + 0.57 * K / 64 + (dual_F > 0 ? 0.0 : 4.0);
+        const double t_split = 12.0 + 1.05 * per * tk / 64 + 0.42e-6 * 4.0 * ks * M * ncols;
+        if (small > 256 || t_split >= t_small) return 1;
+    }
     *krange = per * tk;
     return (stages + per - 1) / per;
 }

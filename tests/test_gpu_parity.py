@@ -516,3 +516,27 @@ def test_fused_rope_epilogue_bit_exact(case):
             outs.append((bf16_to_np(y),) + fp.export_kv(0))
     for a, b in zip(*outs):
         assert (a is None and b is None) or np.array_equal(a, b)
+
+
+# Prompts of less than one 256-row tile take split-K on the large tiling where K is long and
+# the columns few: the down projection (ffn 4096), the [gate; up] projection (hidden 4096); two
+# tokens, one row short of a tile, one sequence and several; the reductions carry the norms
+# of both layers.  One token (M = 1) keeps the small tiling.
+SMALL_SPLIT_CASES = [
+    ("down-bf16", Shape(2, 512, 4, 4, 128, 4096, 3, 85, 87), "bf16", "bf16", 3, 85),
+    ("down-int4-two-tokens", Shape(2, 512, 4, 4, 128, 4096, 1, 2, 4), "int4", "int8", 1, 2),
+    ("gate-up-int4", Shape(2, 4096, 4, 4, 128, 512, 1, 63, 65), "int4", "bf16", 1, 63),
+    ("gate-up-int8", Shape(2, 4096, 4, 4, 128, 512, 2, 50, 52), "int8", "int8", 2, 50),
+    ("one-token-bf16", Shape(2, 512, 4, 4, 128, 4096, 1, 1, 3), "bf16", "bf16", 1, 1),
+]
+
+
+@pytest.mark.parametrize("case", SMALL_SPLIT_CASES, ids=[c[0] for c in SMALL_SPLIT_CASES])
+def test_parity_small_prompt_split(case):
+    name, shape, wq, kvq, B, P = case
+    log(f"case {name}: {shape} {wq}/{kvq} B={B} P={P}")
+    res = run_parity(shape, wq, kvq, B, P, 1, layerwise=True)
+    _report(name, res)
+    assert res.prefill_err <= TOL
+    assert all(e <= TOL for e in res.layer_errs)
+    assert max(res.decode_errs) <= TOL
