@@ -262,7 +262,7 @@ def roofline_entry(kernel, bound, achieved, peak, unit, avg_ms, per_launch, traf
 
 def run_workload(name, args, torch, timed_out=None):
     """Measure one workload: W warm-up passes, K timed passes (a pass is a prefill and S
-    decode steps in one fp_decode_steps call), one pass with a graph per decode step for
+    decode steps in one fp_decode_steps call), one pass with one call per decode step for
     the step-time distribution, and one eagerly profiled prefill and eight decode steps
     for the per-kernel figures."""
     from paper_2501_13111_amd import Fingerprint, fill_normal
@@ -308,7 +308,7 @@ def run_workload(name, args, torch, timed_out=None):
     mean_bytes = statistics.fmean(decode_step_bytes(s, wq, kvq, B, Pp + i) for i in range(S))
     step_frac = mean_bytes / (statistics.fmean(pass_step_ms) / 1e3) / 1e9 / HBM_PEAK_GBS
 
-    # ---- step-time distribution: one pass with one graph replay per decode step
+    # ---- step-time distribution: one pass with one call per decode step
     fp.prefill(x, y, B, Pp)
     bufs[0].copy_(y.view(B, Pp, H)[:, -1, :].reshape(-1))
     sev = [torch.cuda.Event(enable_timing=True) for _ in range(S + 1)]
@@ -389,7 +389,7 @@ def run_workload(name, args, torch, timed_out=None):
         "decode_step_us": round(1e3 * statistics.median(pass_step_ms), 2),
         "decode_step_timing": "median over passes of the pass's mean step (the S steps run as one call)",
         "decode_step_us_p10_p50_p90": [round(1e3 * pct(q), 2) for q in (0.1, 0.5, 0.9)],
-        "decode_step_single_timing": "one pass, one graph replay per step (adds one graph launch per step)",
+        "decode_step_single_timing": "one pass, one call per step (its kernels launched one by one)",
         "decode_step_hbm_frac": round(step_frac, 4),
         "decode_step_algorithmic_MB": round(mean_bytes / 1e6, 2),
         "prefill_ms": round(pre_med, 4),

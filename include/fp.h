@@ -150,8 +150,8 @@ fp_status fp_decode_step(fp_layer* layer, const void* x, void* y, void* stream);
  * step 2 reads y and writes x, and so on: the last step's output ends in y when n
  * is odd and in x when n is even.  x and y: device bf16 [B, hidden] each, both
  * written, no aliasing.  With the decode graph on (fp_set_decode_graph), the n
- * steps are captured once per (x, y, n) and replayed as one graph, which saves a
- * graph launch per step; the results equal n calls of fp_decode_step.  The
+ * steps are captured once per (x, y, n) and replayed as one graph, which saves the
+ * steps' launches; the results equal n calls of fp_decode_step.  The
  * position advances by n.  FP_ERR_INVALID_ARG for n < 1, NULL or overlapping
  * buffers; FP_ERR_STATE before a prefill; FP_ERR_CAPACITY when fewer than n
  * positions remain before max_seq (nothing runs).
@@ -174,11 +174,12 @@ fp_status fp_decode_steps(fp_layer* layer, void* x, void* y, int32_t n, void* st
 fp_status fp_decode_step_noalloc(fp_layer* layer, const void* x, void* y, void* stream);
 
 /*
- * Replay decode steps as a captured HIP graph (1, the default) or launch the
- * kernels one by one (0).  Results are identical.  Graphs are captured on first
- * use per (x, y, active batch) for fp_decode_step and per (x, y, n, active batch)
- * for fp_decode_steps; each cache holds at most 16 graphs and is emptied (after a
- * device synchronisation) when a new capture would exceed that.
+ * Replay the steps of fp_decode_steps and fp_generate as a captured HIP graph (1, the
+ * default) or launch the kernels one by one (0).  Results are identical.  Graphs are
+ * captured on first use per (x, y, n, active batch) for fp_decode_steps; each cache holds
+ * at most 16 graphs and is emptied (after a device synchronisation) when a new capture
+ * would exceed that.  fp_decode_step always launches its kernels one by one (a graph per
+ * single step takes longer); with 1 it refuses a stream that is being captured.
  */
 fp_status fp_set_decode_graph(fp_layer* layer, int32_t enable);
 

@@ -189,11 +189,10 @@ struct fp_layer {
     float* dump = nullptr;
     uint16_t* ldump = nullptr;      // per-layer outputs [n_layers, B, T, hidden] (debug)
     hipStream_t cap_stream = nullptr;
-    // Captured decode graphs.  A capture bakes in the buffers and everything that depends
-    // on the active batch (grids, split factors, the single-sequence or batch schedule,
-    // the rows written), so both caches are keyed by the batch too, and a prefill that
+    // Captured graphs of several decode steps.  A capture bakes in the buffers and everything
+    // that depends on the active batch (grids, split factors, the single-sequence or batch
+    // schedule, the rows written), so both caches are keyed by the batch too, and a prefill that
     // changes the batch drops them.  At most GRAPH_CACHE_MAX entries each.
-    std::map<std::tuple<const void*, void*, int>, hipGraphExec_t> graphs;     // (x, y, B)
     std::map<std::tuple<void*, void*, int, int>, hipGraphExec_t> mgraphs;     // (x, y, n, B)
     // fp_generate's decode loop: (out_ids, logits, force_ids, n_out, B)
     std::map<std::tuple<int32_t*, float*, const int32_t*, int, int>, hipGraphExec_t> ggraphs;
@@ -235,10 +234,8 @@ constexpr size_t GRAPH_CACHE_MAX = 16;
 // Destroy every captured decode graph.  A replay may still be in flight on some stream,
 // so the device is synchronised first (only when there is something to destroy).
 void drop_graphs(fp_layer* h) {
-    if (h->graphs.empty() && h->mgraphs.empty() && h->ggraphs.empty()) return;
+    if (h->mgraphs.empty() && h->ggraphs.empty()) return;
     (void)hipDeviceSynchronize();
-    for (auto& kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
-    h->graphs.clear();
     for (auto& kv : h->mgraphs) (void)hipGraphExecDestroy(kv.second);
     h->mgraphs.clear();
     for (auto& kv : h->ggraphs) (void)hipGraphExecDestroy(kv.second);
@@ -1231,30 +1228,18 @@ fp_status fp_decode_step(fp_layer* h, const void* x, void* y, void* stream) {
     if (!h->unbacked) {
         hipStream_t st = (hipStream_t)stream;
         fp_status rc;
+        // One step is launched kernel by kernel: its launches (2.5 us each on the host) run ahead
+        // of its kernels, while a graph launch per step left the GPU idle for about 4 us between
+        // steps (tiny fingerprint, 16 calls after a prefill: 512 us with a graph per step, 452
+        // without; a grouped-query layer, 7 sequences, 9 calls: 660 and 606).  With the decode
+        // graph on, a stream under capture is refused, as replaying a graph into it was.
         if (h->use_graph && !h->dump && !h->ldump) {
-            const auto key = std::make_tuple(x, y, h->B);
-            auto it = h->graphs.find(key);
-            if (it == h->graphs.end()) {
-                if (h->graphs.size() >= GRAPH_CACHE_MAX) drop_graphs(h);
-                hipGraph_t g = nullptr;
-                hipGraphExec_t ge = nullptr;
-                HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-                rc = enqueue_decode(h, (const uint16_t*)x, (uint16_t*)y, h->cap_stream);
-                hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
-                if (rc) {
-                    if (g) (void)hipGraphDestroy(g);
-                    return rc;
-                }
-                if (e != hipSuccess) return fail(FP_ERR_HIP, "graph capture failed: %s", hipGetErrorString(e));
-                e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-                (void)hipGraphDestroy(g);
-                if (e != hipSuccess) return fail(FP_ERR_HIP, "graph instantiate failed: %s", hipGetErrorString(e));
-                it = h->graphs.emplace(key, ge).first;
-            }
-            HIPCHK(hipGraphLaunch(it->second, st));
-        } else {
-            if ((rc = enqueue_decode(h, (const uint16_t*)x, (uint16_t*)y, st))) return rc;
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            HIPCHK(hipStreamIsCapturing(st, &cs));
+            if (cs != hipStreamCaptureStatusNone)
+                return fail(FP_ERR_HIP, "decode step on a capturing stream with the decode graph on");
         }
+        if ((rc = enqueue_decode(h, (const uint16_t*)x, (uint16_t*)y, st))) return rc;
     }
     h->pos += 1;
     return FP_OK;

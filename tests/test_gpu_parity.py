@@ -540,3 +540,28 @@ def test_parity_small_prompt_split(case):
     assert res.prefill_err <= TOL
     assert all(e <= TOL for e in res.layer_errs)
     assert max(res.decode_errs) <= TOL
+
+
+def test_decode_step_refuses_a_capturing_stream():
+    """With the decode graph on, a single step on a stream under capture is refused before any
+    launch and leaves the position as it was; outside the capture it runs."""
+    import torch
+    from paper_2501_13111_amd import Fingerprint, FpError, fill_normal
+    shape = Shape(1, 256, 4, 2, 64, 384, 1, 8, 12)
+    with Fingerprint(shape, "bf16", "bf16", seed=1) as fp:
+        x = torch.empty(8 * 256, dtype=torch.bfloat16, device="cuda")
+        fill_normal(x, 1, -1, 15, 0.0, 1.0)
+        y = torch.empty_like(x)
+        fp.prefill(x, y, 1, 8)
+        a = y.view(1, 8, 256)[:, -1, :].contiguous()
+        b = torch.zeros_like(a)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            b.zero_()
+            with pytest.raises(FpError):
+                fp.decode_step(a, b)
+        assert fp.position() == (8, 1)
+        fp.decode_step(a, b)
+        torch.cuda.synchronize()
+        assert fp.position() == (9, 1) and bool((b != 0).any())
