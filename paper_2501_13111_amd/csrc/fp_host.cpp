@@ -604,7 +604,8 @@ fp_status enqueue_prefill(fp_layer* h, const uint16_t* x, int B, int P, uint16_t
     const float scale = (float)(1.0 / std::sqrt((double)s.head_dim));
     fp_status rc;
     const int H = s.hidden, F = s.ffn;
-    int kr_o, kr_g, kr_d;
+    int kr_q, kr_o, kr_g, kr_d;
+    const int ks_q = gemm_qkv_split_factor(M, h->nqkv, H, h->wq, &kr_q);
     const int ks_o = prefill_split(h, M, H, h->q_dim, 0, &kr_o);
     const int ks_g = prefill_split(h, M, 2 * F, H, F, &kr_g);
     const int ks_d = prefill_split(h, M, H, F, 0, &kr_d);
@@ -621,12 +622,14 @@ fp_status enqueue_prefill(fp_layer* h, const uint16_t* x, int B, int P, uint16_t
         }
         normed = false;
         h->prof.mark(FP_K_QKV, l);
-        const RopeKvArgs ro = rope_args(h, l, h->qkv32, 1, M, P, nullptr, dump);
+        const RopeKvArgs ro = rope_args(h, l, ks_q > 1 ? h->ppart : h->qkv32, ks_q, M, P, nullptr, dump);
         if (!dump && gemm_rope_supported(M, W.qkv.N, W.qkv.K, P, s.head_dim, W.qkv.wf)) {
             // rotary embedding and KV append in the projection's epilogue
             if ((rc = run_gemm(h, h->act_in, W.qkv, M, EPI_ROPE, nullptr, nullptr, nullptr, st, &ro))) return rc;
         } else {
-            if ((rc = run_gemm(h, h->act_in, W.qkv, M, EPI_F32, h->qkv32, nullptr, nullptr, st))) return rc;
+            if (ks_q > 1) rc = run_gemm_split(h, h->act_in, W.qkv, M, 0, ks_q, kr_q, h->ppart, st);
+            else rc = run_gemm(h, h->act_in, W.qkv, M, EPI_F32, h->qkv32, nullptr, nullptr, st);
+            if (rc) return rc;
             h->prof.mark(FP_K_ROPE_KV, l);
             HIPCHK(launch_rope_kv(ro, st));
         }
@@ -1010,10 +1013,11 @@ fp_status alloc_storage(fp_layer* h) {
         const int Mp = (int)act_elems(h);
         for (int M = std::min(2, Mp); M > 0; M = M == Mp ? 0 : M < 256 ? M + 1 : std::min(M + 256, Mp)) {
             int kr;
+            const int kq = gemm_qkv_split_factor(M, h->nqkv, H, h->wq, &kr);
             const int ko = prefill_split(h, M, H, h->q_dim, 0, &kr);
             const int kg = prefill_split(h, M, 2 * F, H, F, &kr);
             const int kd = prefill_split(h, M, H, F, 0, &kr);
-            pp = std::max({pp, (size_t)(ko > 1 ? ko : 0) * M * H, (size_t)(kg > 1 ? kg : 0) * M * 2 * F,
+            pp = std::max({pp, (size_t)(kq > 1 ? kq : 0) * M * h->nqkv, (size_t)(ko > 1 ? ko : 0) * M * H, (size_t)(kg > 1 ? kg : 0) * M * 2 * F,
                            (size_t)(kd > 1 ? kd : 0) * M * H});
         }
         if (pp > 0 && (st = alloc_t(h, &h->ppart, pp, &h->bytes_ws))) return st;

@@ -217,6 +217,8 @@ hipError_t launch_gemm_rope(const GemmArgs& a, const RopeKvArgs& ro, int wf, hip
 // the GPU: the split factor (1: no split) and k per split for an [M, N] x [N, K]
 // product (dual_F > 0: the [gate; up] matrix), and the launch writing EPI_PART partials.
 int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange);
+// The same for the qkv projection, whose partials launch_rope_kv sums.
+int gemm_qkv_split_factor(int M, int N, int K, int wf, int* krange);
 hipError_t launch_gemm_split(const GemmArgs& a, int wf, bool dual, int ks, hipStream_t st);
 
 int attn_decode_max_splits(int max_seq);

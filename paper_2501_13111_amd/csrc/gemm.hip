@@ -1028,6 +1028,38 @@ int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange) {
     return (stages + per - 1) / per;
 }
 
+// The qkv projection of a prompt below the large tiling's threshold, whose reduction is the
+// rotary kernels: they read all ks partials, so the factor is the cheapest of the model below
+// rather than the largest that fits.  In us, fitted to 256 to 1024 rows of K 768 to 8192 (bf16
+// and int8): the split GEMM 7 + 1.1 per 64 inputs + 0.17 per MB of partials written, 0.25 per
+// MB read beyond the first; the small tiling 3 + K / 64 times 0.55 on one workgroup per
+// compute unit or fewer, 0.4 + 0.27 w on w of them.  Small tiling / split GEMM, us: bf16
+// 12288 x 4096 300 rows 67.7 / 40.4, 512 rows 73.6 / 48.8; 6144 x 4096 512 rows 52.4 / 35.7;
+// int8 10240 x 8192 512 rows 125 / 73.4, 1280 x 8192 67.5 / 23.1; but 768 x 768 10.0 / 11.8
+// and 3072 x 2048 21.0 / 19.1 before the reads.  Int4 stays on the small tiling, whose
+// accumulation differs from the partials'.
+int gemm_qkv_split_factor(int M, int N, int K, int wf, int* krange) {
+    const int rows = (M + BT - 1) / BT, tiles = rows * ((N + BT - 1) / BT);
+    const int tk = big_tk(wf);
+    *krange = K;
+    if (M < 2 || (wf != W_BF16 && wf != W_INT8) || tiles >= GEMM_BIG_MIN_TILES || K % tk != 0) return 1;
+    const int stages = K / tk;
+    const double w = ((M + 63) / 64) * ((N + GBN - 1) / GBN) / 256.0;
+    double best = 3.0 + K / 64.0 * (w <= 1.0 ? 0.55 : std::max(0.55, 0.4 + 0.27 * w)) - 2.0;
+    const double mb = 4e-6 * rows * BT * N;      // one partial, whole row tiles: the factor depends on those only
+    int ks = 1;
+    for (int k = 2; k <= GEMM_SPLIT_MAX && k * tiles <= 256 && k * 4 <= stages; ++k) {
+        const int per = (stages + k - 1) / k, n = (stages + per - 1) / per;
+        const double t = 7.0 + 1.1 * per * tk / 64 + 0.17 * n * mb + 0.25 * (n - 1) * mb;
+        if (t < best) {
+            best = t;
+            ks = n;
+            *krange = per * tk;
+        }
+    }
+    return ks;
+}
+
 hipError_t launch_gemm_split(const GemmArgs& a, int wf, bool dual, int ks, hipStream_t st) {
     if (ks < 1 || a.krange <= 0 || a.krange % big_tk(wf) != 0 || a.K % big_tk(wf) != 0 || (int64_t)ks * a.krange < a.K ||
         (int64_t)(ks - 1) * a.krange >= a.K)

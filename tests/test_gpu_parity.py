@@ -542,6 +542,29 @@ def test_parity_small_prompt_split(case):
     assert max(res.decode_errs) <= TOL
 
 
+# The qkv projection of a prompt below the large tiling's threshold: split-K partials summed by
+# the rotary and KV append kernels.  Two tokens, one tile row and one row more, several
+# sequences, value blocks of fewer than 32 positions, head_dim 64, a long K (16 partials).
+QKV_SPLIT_CASES = [
+    ("bf16-two-tokens", Shape(1, 4096, 4, 1, 128, 512, 1, 2, 4), "bf16", "bf16", 1, 2),
+    ("bf16-257", Shape(1, 4096, 4, 1, 128, 512, 1, 257, 259), "bf16", "bf16", 1, 257),
+    ("bf16-int8kv-3x85", Shape(2, 4096, 8, 2, 64, 512, 3, 85, 87), "bf16", "int8", 3, 85),
+    ("int8-2x160", Shape(1, 4096, 6, 2, 128, 512, 2, 160, 162), "int8", "bf16", 2, 160),
+    ("int8-int8kv-16-partials", Shape(1, 8192, 4, 1, 128, 512, 1, 96, 98), "int8", "int8", 1, 96),
+]
+
+
+@pytest.mark.parametrize("case", QKV_SPLIT_CASES, ids=[c[0] for c in QKV_SPLIT_CASES])
+def test_parity_qkv_split(case):
+    name, shape, wq, kvq, B, P = case
+    log(f"case {name}: {shape} {wq}/{kvq} B={B} P={P}")
+    res = run_parity(shape, wq, kvq, B, P, 1, layerwise=True)
+    _report(name, res)
+    assert res.prefill_err <= TOL
+    assert all(e <= TOL for e in res.layer_errs)
+    assert max(res.decode_errs) <= TOL
+
+
 def test_decode_step_refuses_a_capturing_stream():
     """With the decode graph on, a single step on a stream under capture is refused before any
     launch and leaves the position as it was; outside the capture it runs."""
