@@ -1011,6 +1011,21 @@ int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange) {
     if (ks > GEMM_SPLIT_MAX) ks = GEMM_SPLIT_MAX;
     if (ks > stages / 4) ks = stages / 4;
     if (ks < 2) return 1;
+    if (M >= BT) {
+        // Fewer partials where writing and reading them costs more than the shorter k ranges save
+        // (in us, the model of gemm_qkv_split_factor).  4096 x 4096 with its reduction at 512 rows:
+        // 8 partials 42 to 47, 4 partials 42; a bf16 layer of hidden 4096, 512 rows: 320 -> 316.
+        const double mb = 4e-6 * ((M + BT - 1) / BT) * BT * (dual_F > 0 ? 2.0 * dual_F : N);
+        double best = 1e30;
+        for (int k = 2, kmax = ks; k <= kmax; ++k) {
+            const int per = (stages + k - 1) / k, n = (stages + per - 1) / per;
+            const double t = 1.1 * per * tk / 64 + (0.17 + 0.25) * n * mb;
+            if (t < best) {
+                best = t;
+                ks = n;
+            }
+        }
+    }
     const int per = (stages + ks - 1) / ks;
     if (M < BT) {
         // Less than one row tile: the small tiling walks K on few workgroups (0.57 us per 64
