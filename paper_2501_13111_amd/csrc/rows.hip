@@ -217,7 +217,9 @@ __global__ void __launch_bounds__(256) swiglu_kernel(const float* __restrict__ p
 // rounded to nearest even once here), one thread per two rotation pairs
 // (j, j + d/2) and (j + 1, j + 1 + d/2), so that every store is a whole dword.
 #pragma clang fp contract(off)
-template <bool F16>
+// SPLIT: ks > 1, a kernel of its own (the loop over partials costs 2 to 5% of a small prefill of
+// one partial: 7B 2:4, 4 x 500 tokens, 725 -> 736 us).
+template <bool F16, bool SPLIT>
 __global__ void __launch_bounds__(256) rope_q_kernel(const float* __restrict__ qkv, int ks, int M, int T, int nh,
                                                       int nkv, int d, const float* __restrict__ cos_t,
                                                       const float* __restrict__ sin_t, uint16_t* __restrict__ qout) {
@@ -232,12 +234,14 @@ __global__ void __launch_bounds__(256) rope_q_kernel(const float* __restrict__ q
         const int pos = (int)(m % T);
         const float* p = qkv + m * Nqkv + (int64_t)h * d;
         float2 u = *(const float2*)(p + j), v = *(const float2*)(p + j + half);
+        if constexpr (SPLIT) {
 #pragma unroll 4
-        for (int k = 1; k < ks; ++k) {
-            const float* pk = p + (int64_t)k * M * Nqkv + j;
-            const float2 uk = *(const float2*)pk, vk = *(const float2*)(pk + half);
-            u.x += uk.x; u.y += uk.y;
-            v.x += vk.x; v.y += vk.y;
+            for (int k = 1; k < ks; ++k) {
+                const float* pk = p + (int64_t)k * M * Nqkv + j;
+                const float2 uk = *(const float2*)pk, vk = *(const float2*)(pk + half);
+                u.x += uk.x; u.y += uk.y;
+                v.x += vk.x; v.y += vk.y;
+            }
         }
         const float2 c = *(const float2*)(cos_t + (int64_t)pos * half + j);
         const float2 s = *(const float2*)(sin_t + (int64_t)pos * half + j);
@@ -256,12 +260,11 @@ __global__ void __launch_bounds__(256) rope_q_kernel(const float* __restrict__ q
 // ([d][VT_BLK], slot vt_slot(kb)) and written out as one contiguous block.  int8:
 // s = fp16(absmax/127), code = rint(v/s) per (position, kv head), separately for K
 // and V.  Slots past the prompt are cleared.  Lane j handles dims j and j + d/2
-// (d <= 128); wave w handles positions w, w + KVA_WAVES, ... of the block.  Bound by the
-// latency of its loads where blocks are few (a tensor-parallel rank has one kv head): hence
-// 16 waves, two positions each, rather than 4.
-constexpr int KVA_WAVES = 16;
-template <bool KV8>
-__global__ void __launch_bounds__(KVA_WAVES * 64) kv_append_kernel(const float* __restrict__ qkv, int ks, int M, int T, int nh,
+// (d <= 128); wave w handles positions w, w + NW, ... of the block.  Bound by the latency of
+// its loads where blocks are few and partials many (a tensor-parallel rank has one kv head):
+// so SPLIT (ks > 1) takes 16 waves, two positions each, else 4.
+template <bool KV8, bool SPLIT, int NW = SPLIT ? 16 : 4>
+__global__ void __launch_bounds__(NW * 64) kv_append_kernel(const float* __restrict__ qkv, int ks, int M, int T, int nh,
                                                          int nkv, int d, const float* __restrict__ cos_t,
                                                          const float* __restrict__ sin_t, int kv_stride, int nblk,
                                                          void* __restrict__ kc, void* __restrict__ vc,
@@ -276,7 +279,7 @@ __global__ void __launch_bounds__(KVA_WAVES * 64) kv_append_kernel(const float* 
     const int kcol = nh * d + kvh * d, vcol = nh * d + nkv * d + kvh * d;
     const int64_t crow0 = ((int64_t)b * nkv + kvh) * kv_stride;
     const int j = lane;
-    for (int kb = w; kb < VT_BLK; kb += KVA_WAVES) {
+    for (int kb = w; kb < VT_BLK; kb += NW) {
         const int pos = pb * VT_BLK + kb;
         const int slot = vt_slot(kb);
         if (pos >= T) {
@@ -291,19 +294,25 @@ __global__ void __launch_bounds__(KVA_WAVES * 64) kv_append_kernel(const float* 
         float k0 = 0.f, k1 = 0.f, v0 = 0.f, v1 = 0.f;
         if (j < half) {
             float u = p[kcol + j], x = p[kcol + j + half];
-            v0 = p[vcol + j];
-            v1 = p[vcol + j + half];
+            if constexpr (SPLIT) {
+                v0 = p[vcol + j];
+                v1 = p[vcol + j + half];
 #pragma unroll 4
-            for (int k = 1; k < ks; ++k) {
-                const float* pk = p + (int64_t)k * M * Nqkv + j;
-                u += pk[kcol];
-                x += pk[kcol + half];
-                v0 += pk[vcol];
-                v1 += pk[vcol + half];
+                for (int k = 1; k < ks; ++k) {
+                    const float* pk = p + (int64_t)k * M * Nqkv + j;
+                    u += pk[kcol];
+                    x += pk[kcol + half];
+                    v0 += pk[vcol];
+                    v1 += pk[vcol + half];
+                }
             }
             const float c = cos_t[(int64_t)pos * half + j], s = sin_t[(int64_t)pos * half + j];
             k0 = __fsub_rn(__fmul_rn(u, c), __fmul_rn(x, s));
             k1 = __fadd_rn(__fmul_rn(x, c), __fmul_rn(u, s));
+            if constexpr (!SPLIT) {
+                v0 = p[vcol + j];
+                v1 = p[vcol + j + half];
+            }
             if (dump) {   // [2, M, nkv, d]: dump[0] = K, dump[1] = V
                 float* dk = dump + (m * nkv + kvh) * d;
                 float* dv = dump + (int64_t)M * nkv * d + (m * nkv + kvh) * d;
@@ -340,7 +349,7 @@ __global__ void __launch_bounds__(KVA_WAVES * 64) kv_append_kernel(const float* 
     const int esz = KV8 ? 1 : 2;
     const int nchunk = d * VT_BLK * esz / 16;
     u32x4* dst = (u32x4*)((char*)vc + (((int64_t)b * nkv + kvh) * nblk + pb) * d * VT_BLK * esz);
-    for (int c = threadIdx.x; c < nchunk; c += KVA_WAVES * 64) dst[c] = ((const u32x4*)vt)[c];
+    for (int c = threadIdx.x; c < nchunk; c += NW * 64) dst[c] = ((const u32x4*)vt)[c];
 }
 #pragma clang fp contract(on)
 
@@ -388,21 +397,24 @@ hipError_t launch_rope_kv(const RopeKvArgs& a, hipStream_t st) {
     if (a.d % 4 != 0) return hipErrorInvalidValue;
     const int64_t pairs = (int64_t)a.M * a.nh * (a.d / 4);
     const int nb = (int)std::min<int64_t>((pairs + 255) / 256, 8192);
-    if (a.kv_int8)
-        FP_LAUNCH(rope_q_kernel<true>, dim3(nb), dim3(256), 0, st, a.part, a.ks, a.M, a.T, a.nh, a.nkv, a.d, a.cos_t,
-                  a.sin_t, a.qout);
-    else
-        FP_LAUNCH(rope_q_kernel<false>, dim3(nb), dim3(256), 0, st, a.part, a.ks, a.M, a.T, a.nh, a.nkv, a.d, a.cos_t,
-                  a.sin_t, a.qout);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     const dim3 grid((a.T + VT_BLK - 1) / VT_BLK, a.nkv, a.M / a.T);
-    if (a.kv_int8)
-        FP_LAUNCH(kv_append_kernel<true>, grid, dim3(KVA_WAVES * 64), 0, st, a.part, a.ks, a.M, a.T, a.nh, a.nkv, a.d, a.cos_t,
-                  a.sin_t, a.kv_stride, a.nblk, a.kc, a.vc, a.ks_out, a.vs_out, a.dump);
-    else
-        FP_LAUNCH(kv_append_kernel<false>, grid, dim3(KVA_WAVES * 64), 0, st, a.part, a.ks, a.M, a.T, a.nh, a.nkv, a.d, a.cos_t,
-                  a.sin_t, a.kv_stride, a.nblk, a.kc, a.vc, a.ks_out, a.vs_out, a.dump);
+#define FP_ROPE_KV(I8, SPLIT)                                                                                       \
+    do {                                                                                                            \
+        FP_LAUNCH((rope_q_kernel<I8, SPLIT>), dim3(nb), dim3(256), 0, st, a.part, a.ks, a.M, a.T, a.nh, a.nkv, a.d, \
+                  a.cos_t, a.sin_t, a.qout);                                                                        \
+        hipError_t e = hipGetLastError();                                                                           \
+        if (e != hipSuccess) return e;                                                                              \
+        FP_LAUNCH((kv_append_kernel<I8, SPLIT>), grid, dim3(SPLIT ? 1024 : 256), 0, st, a.part, a.ks, a.M, a.T,     \
+                  a.nh, a.nkv, a.d, a.cos_t, a.sin_t, a.kv_stride, a.nblk, a.kc, a.vc, a.ks_out, a.vs_out, a.dump); \
+    } while (0)
+    if (a.ks > 1) {
+        if (a.kv_int8) FP_ROPE_KV(true, true);
+        else FP_ROPE_KV(false, true);
+    } else {
+        if (a.kv_int8) FP_ROPE_KV(true, false);
+        else FP_ROPE_KV(false, false);
+    }
+#undef FP_ROPE_KV
     return hipGetLastError();
 }
 
