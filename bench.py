@@ -45,16 +45,16 @@ PROJ = {"qkv", "o", "gate_up", "down"}
 # were taken on (hash of the kernel's source files and of its argument block in
 # fp_internal.h); the summaries and commands are in profiles/.
 TRAFFIC = {
-    ("prefill_gemm", "llama2-70b-tp8-int4"): {"src": "ef13af709f851df1", "bytes_per_launch": 8605742090},
-    ("prefill_attn", "llama2-70b-tp8-int4"): {"src": "4c143c5591b38ef6", "bytes_per_launch": 1622333522},
-    ("decode_proj", "llama2-70b-tp8-int4"): {"src": "7bbc74de5f69e243", "bytes_per_launch": 27162882},
-    ("decode_attn", "llama2-70b-tp8-int4"): {"src": "3348a08a368fc693", "bytes_per_launch": 47377051},
+    ("prefill_gemm", "llama2-70b-tp8-int4"): {"src": "fe37974026cf516b", "bytes_per_launch": 8838799402},
+    ("prefill_attn", "llama2-70b-tp8-int4"): {"src": "728c82f264714b03", "bytes_per_launch": 1623881112},
+    ("decode_proj", "llama2-70b-tp8-int4"): {"src": "7bbc74de5f69e243", "bytes_per_launch": 27162885},
+    ("decode_attn", "llama2-70b-tp8-int4"): {"src": "5240dca1acd310c1", "bytes_per_launch": 47376932},
     ("decode_proj", "llama2-7b-bf16"): {"src": "7bbc74de5f69e243", "bytes_per_launch": 102930905},
 }
 FAMILY_SRC = {
     "decode_proj": (("skinny.hip", "fp_device.h"), r"enum XForm \{.*?\n\};\n.*?struct SkinnyArgs \{.*?\n\};"),
-    "prefill_gemm": (("gemm.hip", "fp_device.h"), r"struct GemmArgs \{.*?\n\};"),
-    "prefill_attn": (("attn_prefill.hip", "fp_device.h"), r"struct AttnPreArgs \{.*?\n\};"),
+    "prefill_gemm": (("gemm.hip", "lds_copy.h", "fp_device.h"), r"struct GemmArgs \{.*?\n\};"),
+    "prefill_attn": (("attn_prefill.hip", "lds_copy.h", "fp_device.h"), r"struct AttnPreArgs \{.*?\n\};"),
     "decode_attn": (("attn_decode.hip", "fp_device.h"), r"struct AttnDecArgs \{.*?\n\};"),
 }
 

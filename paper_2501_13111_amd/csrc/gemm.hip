@@ -13,7 +13,8 @@
 //           exact q - z with the group scale on the fp32 accumulators  (fp16 MFMA)
 // Epilogues: fp32 store (q, k, v before the rotary embedding), residual
 // out = bf16(resid + acc), and SwiGLU a = bf16(silu(gate) * up) where each wave
-// holds gate and up columns of the same f (dual tiles over [gate; up]).
+// holds gate and up columns of the same f (dual tiles over [gate; up]); on the large
+// tiling also the rotary embedding with the KV append, and split-K partials.
 //
 // Weights are read from the fragment-major layout (1 KiB blocks of 16 rows x one
 // K-step), so each 64-thread group of a tile load reads contiguous memory.
