@@ -169,6 +169,7 @@ struct fp_layer {
     float* part = nullptr;        // decode split-K partials              [KSMAX, Bmax, Ncol]
     float* part2 = nullptr;       // gate|up partials (read while down writes part)
     float* ppart = nullptr;       // prefill split-K partials (GEMMs with too few large tiles)
+    size_t ppart_elems = 0;
     float* attn_ws = nullptr;     // decode attention partials
     float* ssq = nullptr;         // decode row-norm block sums         [Bmax, nblk]
     int* d_pos = nullptr;
@@ -580,7 +581,10 @@ int prefill_split(const fp_layer* h, int M, int N, int K, int dual_F, int* krang
 }
 
 fp_status run_gemm_split(fp_layer* h, const uint16_t* X, const Mat& m, int M, int dual_F, int ks, int krange,
-                         float* part, hipStream_t st) {
+                         hipStream_t st) {
+    const size_t need = (size_t)ks * M * m.N;
+    if (need > h->ppart_elems)
+        return fail(FP_ERR_CAPACITY, "%zu split-K partials of a %d-token prefill exceed the %zu allocated", need, M, h->ppart_elems);
     GemmArgs a{};
     a.X = X;
     a.W = m.codes;
@@ -592,7 +596,7 @@ fp_status run_gemm_split(fp_layer* h, const uint16_t* X, const Mat& m, int M, in
     a.K = m.K;
     a.kst = m.kst;
     a.F = h->s.ffn;
-    a.out32 = part;
+    a.out32 = h->ppart;
     a.krange = krange;
     HIPCHK(launch_gemm_split(a, h->wq, dual_F > 0, ks, st));
     return FP_OK;
@@ -627,7 +631,7 @@ fp_status enqueue_prefill(fp_layer* h, const uint16_t* x, int B, int P, uint16_t
             // rotary embedding and KV append in the projection's epilogue
             if ((rc = run_gemm(h, h->act_in, W.qkv, M, EPI_ROPE, nullptr, nullptr, nullptr, st, &ro))) return rc;
         } else {
-            if (ks_q > 1) rc = run_gemm_split(h, h->act_in, W.qkv, M, 0, ks_q, kr_q, h->ppart, st);
+            if (ks_q > 1) rc = run_gemm_split(h, h->act_in, W.qkv, M, 0, ks_q, kr_q, st);
             else rc = run_gemm(h, h->act_in, W.qkv, M, EPI_F32, h->qkv32, nullptr, nullptr, st);
             if (rc) return rc;
             h->prof.mark(FP_K_ROPE_KV, l);
@@ -658,7 +662,7 @@ fp_status enqueue_prefill(fp_layer* h, const uint16_t* x, int B, int P, uint16_t
         h->prof.mark(FP_K_O, l);
         if (ks_o > 1) {
             // split-K partials; the residual add and the MLP RMSNorm in one row kernel
-            if ((rc = run_gemm_split(h, h->act_o, W.o, M, 0, ks_o, kr_o, h->ppart, st))) return rc;
+            if ((rc = run_gemm_split(h, h->act_o, W.o, M, 0, ks_o, kr_o, st))) return rc;
             HIPCHK(launch_resid_norm(h->ppart, ks_o, M, H, in, h->hbuf, W.mlp_norm, s.rms_eps, h->act_in,
                                      h->act_fmt, nullptr, nullptr, st));
         } else {
@@ -668,7 +672,7 @@ fp_status enqueue_prefill(fp_layer* h, const uint16_t* x, int B, int P, uint16_t
         }
         h->prof.mark(FP_K_GATE_UP, l);
         if (ks_g > 1) {
-            if ((rc = run_gemm_split(h, h->act_in, W.gu, M, F, ks_g, kr_g, h->ppart, st))) return rc;
+            if ((rc = run_gemm_split(h, h->act_in, W.gu, M, F, ks_g, kr_g, st))) return rc;
             HIPCHK(launch_swiglu(h->ppart, ks_g, M, F, h->act_f, h->act_fmt, st));
         } else {
             if ((rc = run_gemm(h, h->act_in, W.gu, M, EPI_SWIGLU, nullptr, h->act_f, nullptr, st))) return rc;
@@ -676,7 +680,7 @@ fp_status enqueue_prefill(fp_layer* h, const uint16_t* x, int B, int P, uint16_t
         h->prof.mark(FP_K_DOWN, l);
         if (ks_d > 1) {
             // the residual add, and the next layer's attention RMSNorm
-            if ((rc = run_gemm_split(h, h->act_f, W.down, M, 0, ks_d, kr_d, h->ppart, st))) return rc;
+            if ((rc = run_gemm_split(h, h->act_f, W.down, M, 0, ks_d, kr_d, st))) return rc;
             HIPCHK(launch_resid_norm(h->ppart, ks_d, M, H, h->hbuf, out, last ? nullptr : h->L[l + 1].attn_norm,
                                      s.rms_eps, h->act_in, h->act_fmt, nullptr, nullptr, st));
             normed = !last;
@@ -1006,9 +1010,9 @@ fp_status alloc_storage(fp_layer* h) {
     if ((st = alloc_t(h, &h->part, (size_t)KSMAX * s.max_batch * ncol, &h->bytes_ws))) return st;
     if ((st = alloc_t(h, &h->part2, (size_t)KSMAX * s.max_batch * 2 * F, &h->bytes_ws))) return st;
     {
-        // the largest split-K partial buffer any prefill size up to Mmax asks for (the split
-        // factor depends on the number of 256-row tiles, so the worst case is at a whole tile;
-        // below one tile also on the rows)
+        // the largest split-K partial buffer any prefill size up to Mmax asks for.  From 256 rows
+        // on, the factors never fall as rows are added within a 256-row tile (gemm.hip), so the
+        // worst case of a tile is its last row; below one tile every row count is asked
         size_t pp = 0;
         const int Mp = (int)act_elems(h);
         for (int M = std::min(2, Mp); M > 0; M = M == Mp ? 0 : M < 256 ? M + 1 : std::min(M + 256, Mp)) {
@@ -1020,6 +1024,7 @@ fp_status alloc_storage(fp_layer* h) {
             pp = std::max({pp, (size_t)(kq > 1 ? kq : 0) * M * h->nqkv, (size_t)(ko > 1 ? ko : 0) * M * H, (size_t)(kg > 1 ? kg : 0) * M * 2 * F,
                            (size_t)(kd > 1 ? kd : 0) * M * H});
         }
+        h->ppart_elems = pp;
         if (pp > 0 && (st = alloc_t(h, &h->ppart, pp, &h->bytes_ws))) return st;
     }
     const size_t nch = attn_decode_max_splits(s.max_seq);

@@ -1052,8 +1052,10 @@ int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange) {
 // compute unit or fewer, 0.4 + 0.27 w on w of them.  Small tiling / split GEMM, us: bf16
 // 12288 x 4096 300 rows 67.7 / 40.4, 512 rows 73.6 / 48.8; 6144 x 4096 512 rows 52.4 / 35.7;
 // int8 10240 x 8192 512 rows 125 / 73.4, 1280 x 8192 67.5 / 23.1; but 768 x 768 10.0 / 11.8
-// and 3072 x 2048 21.0 / 19.1 before the reads.  Int4 stays on the small tiling, whose
-// accumulation differs from the partials'.
+// and 3072 x 2048 21.0 / 19.1 before the reads.  Int4 stays on the small tiling: the large one
+// has no partials in the exact int4 scheme that it uses for this projection.
+// Within a 256-row tile the factor never falls as rows are added: the small tiling's time (w)
+// grows and the split's does not depend on the rows.  The partial buffer is sized by that.
 int gemm_qkv_split_factor(int M, int N, int K, int wf, int* krange) {
     const int rows = (M + BT - 1) / BT, tiles = rows * ((N + BT - 1) / BT);
     const int tk = big_tk(wf);
@@ -1062,7 +1064,7 @@ int gemm_qkv_split_factor(int M, int N, int K, int wf, int* krange) {
     const int stages = K / tk;
     const double w = ((M + 63) / 64) * ((N + GBN - 1) / GBN) / 256.0;
     double best = 3.0 + K / 64.0 * (w <= 1.0 ? 0.55 : std::max(0.55, 0.4 + 0.27 * w)) - 2.0;
-    const double mb = 4e-6 * rows * BT * N;      // one partial, whole row tiles: the factor depends on those only
+    const double mb = 4e-6 * rows * BT * N;      // one partial, whole row tiles
     int ks = 1;
     for (int k = 2; k <= GEMM_SPLIT_MAX && k * tiles <= 256 && k * 4 <= stages; ++k) {
         const int per = (stages + k - 1) / k, n = (stages + per - 1) / per;

@@ -1,6 +1,7 @@
 """Host-side tests of the C ABI: the library loads, exports every declared symbol,
 and validates arguments and state on the host (no GPU needed)."""
 import ctypes
+import random
 
 import pytest
 
@@ -286,3 +287,27 @@ def test_estimators_agree_with_the_oracle():
         binding.fit_latency_l2((2, 2), (16, 64), [[1.0, 2.0], [1.0, 2.0]])
     with pytest.raises(FpError):
         binding.extrapolate_layers((3, 3), (1.0, 2.0), 5)
+
+
+def test_split_partials_never_exceed_the_probed_row_counts(lib):
+    """The split-K partial buffer of the prefill is sized over the row counts 2 .. 256 and then
+    over whole 256-row tiles and the largest prefill; every row count between them needs no more."""
+    plain = lib._ZN3fpk17gemm_split_factorEiiiiiPi
+    qkv = lib._ZN3fpk21gemm_qkv_split_factorEiiiiPi
+    for f in (plain, qkv):
+        f.restype = ctypes.c_int
+    kr = ctypes.c_int()
+    rng = random.Random(3)
+    shapes = [(16256, 6912), (12288, 4096), (768, 768), (1280, 8192)]
+    shapes += [(16 * rng.randint(1, 1400), 64 * rng.randint(1, 220)) for _ in range(60)]
+    for N, K in shapes:
+        for wf in (0, 1, 2):
+            k = K if wf < 2 else -(-K // 128) * 128
+            for need in (lambda M: qkv(M, N, k, wf, ctypes.byref(kr)) * M,
+                         lambda M: plain(M, N, k, 0, wf, ctypes.byref(kr)) * M,
+                         lambda M: plain(M, 2 * N, k, N, wf, ctypes.byref(kr)) * M):
+                for last in (rng.randint(257, 1500), 1024):
+                    split = lambda M: need(M) if need(M) > M else 0
+                    probes = [*range(2, 257), *range(512, last, 256), last]
+                    cap = max(split(M) for M in probes)
+                    assert all(split(M) <= cap for M in range(257, last + 1)), (N, K, wf, last)
