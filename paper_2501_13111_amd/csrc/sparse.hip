@@ -95,13 +95,13 @@ hipError_t launch_sp24_compress(const uint16_t* w, int n, int K, uint16_t* vals,
 // they return zeros without memory traffic).  The weight stream should bound it, but each
 // workgroup's prologue does (about a third of a launch): staging M rows instead of the padded
 // 32 or 64, eight pieces in flight, without an index division per piece, took a 7B layer's
-// decode step from 90.0 to 83.4 us at 16 sequences and from 114 to 105 us at 32; four blocks
-// in flight are as fast as eight there and 2% faster at 64.
+// decode step from 86.3 to 80.1 us at 16 sequences, from 105.5 to 94.5 at 32 and from 171 to 148
+// at 64; four blocks in flight are as fast as eight there and 2% faster at 64.
 constexpr int SP_RING = 4;
 constexpr int SP_LDS_BYTES = 64 * 1024;
 constexpr int SP_PAD = 8;
 
-template <int MT>
+template <int MT, bool SPREAD>
 __global__ void __launch_bounds__(256) sp24_gemv_kernel(Sp24Args a) {
     extern __shared__ __attribute__((aligned(16))) uint16_t Xs[];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -122,38 +122,44 @@ __global__ void __launch_bounds__(256) sp24_gemv_kernel(Sp24Args a) {
         ri[d] = a.Wi[(blk0 + min(t, nsteps - 1)) * 64 + lane];
     };
     // The activation slice is staged in batches of eight 16-byte pieces per thread whose loads
-    // are in flight together: a wave takes rows r0, r0 + 4, .. + 12 and of each the pieces
-    // c0 and c0 + 64 (no index division: one per piece cost more than the loads).  The first
-    // batch goes out before the first weight blocks: wait counts are in issue order, so its
-    // arrival does not wait for theirs.
+    // are in flight together, without an index division (one per piece cost more than the loads).
+    // A wave takes a row at a time and of it the pieces of its lanes and those 64 further on.
+    // SPREAD: a row of at most 64 pieces takes only 16, 32 or 64 lanes and one piece of each; the
+    // other lanes take the next rows.  The first batch goes out before the first weight blocks:
+    // wait counts are in issue order, so its arrival does not wait for theirs.
     const int cpr = klen / 8;
+    const int lg = !SPREAD ? 6 : cpr <= 16 ? 4 : cpr <= 32 ? 5 : 6;   // log2 of a row's lanes
+    const int wide = !SPREAD || cpr > 64 ? 1 : 0;
+    const int rpw = 64 >> lg, rstep = 4 * rpw;                         // rows per load of a wave, of the workgroup
+    const int rsub = SPREAD ? lane >> lg : 0, csub = SPREAD ? lane & ((1 << lg) - 1) : lane;
     u32x4 xb[8];
     auto load_x = [&](int r0, int c0) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int row = min(r0 + 4 * (q >> 1), a.M - 1), c = min(c0 + 64 * (q & 1), cpr - 1);
+            const int row = min(r0 + rsub + rstep * (q >> wide), a.M - 1), c = min(c0 + csub + 64 * (q & wide), cpr - 1);
             xb[q] = *(const u32x4*)(a.X + (int64_t)row * a.K + kb + c * 8);
         }
     };
     auto store_x = [&](int r0, int c0) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-            const int row = r0 + 4 * (q >> 1), c = c0 + 64 * (q & 1);
+            const int row = r0 + rsub + rstep * (q >> wide), c = c0 + csub + 64 * (q & wide);
             if (row < a.M && c < cpr) *(u32x4*)(Xs + row * ld + c * 8) = xb[q];
         }
     };
-    const int wv = __builtin_amdgcn_readfirstlane(w);
-    if (wv < a.M) load_x(wv, lane);
+    const int wr = __builtin_amdgcn_readfirstlane(w) * rpw;
+    if (wr < a.M) load_x(wr, 0);
 #pragma unroll
     for (int d = 0; d < SP_RING; ++d) load(d, d);
-    if (wv < a.M) {
-        store_x(wv, lane);
-        for (int c0 = lane + 128; c0 - lane < cpr; c0 += 128) {
-            load_x(wv, c0);
-            store_x(wv, c0);
+    if (wr < a.M) {
+        store_x(wr, 0);
+        for (int c0 = 128; c0 < cpr; c0 += 128) {           // wide rows only
+            load_x(wr, c0);
+            store_x(wr, c0);
         }
-        for (int r0 = wv + 16; r0 < a.M; r0 += 16)
-            for (int c0 = lane; c0 - lane < cpr; c0 += 128) {
+        const int rbatch = (8 >> wide) * rstep;
+        for (int r0 = wr + rbatch; r0 < a.M; r0 += rbatch)
+            for (int c0 = 0; c0 < cpr; c0 += 128) {
                 load_x(r0, c0);
                 store_x(r0, c0);
             }
@@ -203,8 +209,13 @@ hipError_t launch_sp24_gemv(const Sp24Args& a, int ks, hipStream_t st) {
     if ((int64_t)(a.N / 32) * a.kst * 1024 >= ((int64_t)1 << 32) - 16) return hipErrorInvalidValue;
     const dim3 grid((a.N + 127) / 128, ks);
     const size_t lds = (size_t)a.M * (a.krange + SP_PAD) * 2;
-    if (a.M > 32) FP_LAUNCH(sp24_gemv_kernel<2>, grid, dim3(256), lds, st, a);
-    else FP_LAUNCH(sp24_gemv_kernel<1>, grid, dim3(256), lds, st, a);
+    // Rows spread over a wave's lanes from 17 tokens on: with short k-ranges (128 inputs for hidden
+    // 1024) a step of 64 sequences takes 44.5 us, 53.4 with one row per wave, of 17 32.5 and 34.2;
+    // up to 16 one batch holds every row and its wave-uniform addresses are cheaper (tiny
+    // fingerprint, 2 sequences 22.6, 23.6 spread).
+    if (a.M > 32) FP_LAUNCH((sp24_gemv_kernel<2, true>), grid, dim3(256), lds, st, a);
+    else if (a.M > 16) FP_LAUNCH((sp24_gemv_kernel<1, true>), grid, dim3(256), lds, st, a);
+    else FP_LAUNCH((sp24_gemv_kernel<1, false>), grid, dim3(256), lds, st, a);
     return hipGetLastError();
 }
 

@@ -460,13 +460,21 @@ def test_parity_large_tile_edges(case):
     assert max(res.decode_errs) <= TOL
 
 
-@pytest.mark.parametrize("B", [2, 16, 17, 33, 64])
-def test_sp24_decode_batches(B):
-    """The 2:4 decode projection stages exactly B activation rows: one and two 32-token tiles,
-    whole and ragged, with k-ranges of several staging batches (hidden 1152, ffn 2176)."""
-    log(f"sp24 decode B={B}")
+# The 2:4 decode projection stages exactly B activation rows, a row's 16-byte pieces over 16, 32
+# or 64 lanes, or two pieces a lane.  k-ranges of 16 pieces everywhere (hidden 1152, ffn 2176);
+# of 32 pieces, the last one 24 (gate / up of hidden 1984, ffn 4096); of 64, the last one 56 (ffn
+# 8192); of 88, 32 and 172 (the 7B layer).  One and two 32-token tiles, whole and ragged.
+SP24_DECODE_CASES = [(B, 1152, 9, 128, 2176) for B in (2, 16, 17, 33, 64)]
+SP24_DECODE_CASES += [(B, 1984, 31, 64, 4096) for B in (1, 9, 64)]
+SP24_DECODE_CASES += [(B, 1984, 31, 64, 8192) for B in (3, 33)]
+SP24_DECODE_CASES += [(33, 4096, 32, 128, 11008)]
+
+
+@pytest.mark.parametrize("B,hidden,heads,head_dim,ffn", SP24_DECODE_CASES)
+def test_sp24_decode_batches(B, hidden, heads, head_dim, ffn):
+    log(f"sp24 decode B={B} hidden={hidden} ffn={ffn}")
     rows = sorted({0, B // 2, B - 1})
-    res = run_parity(Shape(1, 1152, 9, 9, 128, 2176, B, 6, 8), "sp24", "bf16", B, 6, 2, rows=rows)
+    res = run_parity(Shape(1, hidden, heads, heads, head_dim, ffn, B, 6, 8), "sp24", "bf16", B, 6, 2, rows=rows)
     assert res.prefill_err <= TOL
     assert max(res.decode_errs) <= TOL
 
