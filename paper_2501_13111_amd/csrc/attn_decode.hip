@@ -427,8 +427,7 @@ __global__ void __launch_bounds__(D) attn_merge_kernel(AttnDecArgs a, int nsw) {
 // partials for the consumer to merge), at least one 32-key block each and four
 // splits per pair when the context has four blocks.  The grid depends only on the
 // capacity, so a captured graph replays at every position.
-void attn_decode_split(int max_seq, int B, int nkv, int group, int* nsplit, int* keys_per_split) {
-    (void)group;
+void attn_decode_split(int max_seq, int B, int nkv, int d, int* nsplit, int* keys_per_split) {
 #ifndef FP_ATTN_WAVES
 #define FP_ATTN_WAVES 1024
 #endif
@@ -436,15 +435,18 @@ void attn_decode_split(int max_seq, int B, int nkv, int group, int* nsplit, int*
     const int want = (target + B * nkv - 1) / (B * nkv);
     const int blocks = (max_seq + VT_BLK - 1) / VT_BLK;
     int ns = want < blocks ? want : blocks;
-    // at least the four splits a workgroup holds (its waves would idle otherwise).  A batch
-    // whose context the four waves cover in FP_ATTN_ONE_WG blocks each takes no more, and needs
-    // no merge kernel: 70B-shard step at 64 sequences of 144 positions 75.6 -> 73.9 us, a
-    // grouped-query step of 7 sequences of 144 / 1000 positions 37.5 -> 35.8 / 41.1 -> 40.2 us;
-    // with 8 blocks per wave the longer contexts lose up to 6 us.
-#ifndef FP_ATTN_ONE_WG
-#define FP_ATTN_ONE_WG 4
-#endif
-    if (ns < 4 || (B > 1 && blocks <= 4 * FP_ATTN_ONE_WG)) ns = blocks < 4 ? blocks : 4;
+    // At least the four splits a workgroup holds (its waves would idle otherwise).  A batch whose
+    // context the four waves cover in a few blocks each takes no more: one workgroup per kv head,
+    // and no merge kernel.  That saves about 2 us and costs what the longer walks take, so the line
+    // is at two blocks of head_dim 128, four of 64, and four of either where the kv heads alone make
+    // 96 workgroups.  Step in us, more splits / one workgroup: 4 kv heads of 128, 7 sequences, 132 /
+    // 256 / 512 positions 35.4 33.4 / 35.4 34.5 / 35.8 37.0; 70B shard, 64 sequences, 132 / 320 /
+    // 512 positions 73.6 71.5 / 76.9 77.7 / 77.5 79.3; 2 of 128, 32 sequences (64 workgroups), 512
+    // positions 41.0 41.7; 4 of 128, 32 sequences (128) 45.8 43.5; 6 of 64, 7 sequences, 384
+    // positions 37.9 37.1.
+    const int bpw = (blocks + 3) / 4;
+    const bool one_wg = B > 1 && bpw <= (d == 64 || B * nkv >= 96 ? 4 : 2);
+    if (ns < 4 || one_wg) ns = blocks < 4 ? blocks : 4;
     if (ns < 1) ns = 1;
     const int bps = (blocks + ns - 1) / ns;
     *keys_per_split = bps * VT_BLK;

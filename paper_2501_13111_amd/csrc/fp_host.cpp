@@ -419,7 +419,7 @@ void plan_sp24(const Mat& m, int M, int* ks_out, int* kr_out);
 double qkv_reread(const fp_layer* h, int B) {
     const fp_shape& s = h->s;
     int nsplit = 0, kps = 0;
-    attn_decode_split(s.max_seq, B, s.n_kv_heads, s.n_heads / s.n_kv_heads, &nsplit, &kps);
+    attn_decode_split(s.max_seq, B, s.n_kv_heads, s.head_dim, &nsplit, &kps);
     const int nsw = attn_decode_partials(nsplit);
     return (double)B * s.n_kv_heads * (nsw - 1) * s.n_heads / s.n_kv_heads * s.head_dim * 4.0;
 }
@@ -718,7 +718,7 @@ AttnDecArgs attn_args(fp_layer* h, int l, int ks, int B, float* dump) {
     ad.d_pos = h->d_pos;
     ad.scale = (float)(1.0 / std::sqrt((double)s.head_dim));
     int nsplit;
-    attn_decode_split(s.max_seq, B, s.n_kv_heads, s.n_heads / s.n_kv_heads, &nsplit, &ad.keys_per_split);
+    attn_decode_split(s.max_seq, B, s.n_kv_heads, s.head_dim, &nsplit, &ad.keys_per_split);
     ad.batch = B;
     ad.ws = h->attn_ws;
     ad.out = h->act_o;

@@ -223,7 +223,7 @@ hipError_t launch_gemm_split(const GemmArgs& a, int wf, bool dual, int ks, hipSt
 
 int attn_decode_max_splits(int max_seq);
 int attn_decode_partials(int nsplit);
-void attn_decode_split(int max_seq, int B, int nkv, int group, int* nsplit, int* keys_per_split);
+void attn_decode_split(int max_seq, int B, int nkv, int d, int* nsplit, int* keys_per_split);
 bool attn_decode_supported(int d, int group);
 hipError_t launch_attn_decode(const AttnDecArgs& a, int B, hipStream_t st);
 hipError_t launch_attn_prefill(const AttnPreArgs& a, int B, hipStream_t st);

@@ -311,3 +311,19 @@ def test_split_partials_never_exceed_the_probed_row_counts(lib):
                     probes = [*range(2, 257), *range(512, last, 256), last]
                     cap = max(split(M) for M in probes)
                     assert all(split(M) <= cap for M in range(257, last + 1)), (N, K, wf, last)
+
+
+@pytest.mark.parametrize("seq,B,nkv,d,one", [
+    (132, 7, 4, 128, True), (256, 7, 4, 128, True), (257, 7, 4, 128, False), (320, 64, 1, 128, False),
+    (512, 2, 1, 128, False), (512, 7, 4, 128, False), (512, 16, 4, 128, False), (512, 24, 4, 128, True),
+    (513, 24, 4, 128, False), (512, 7, 6, 64, True), (513, 7, 6, 64, False), (132, 1, 8, 128, False),
+    (2048, 64, 4, 128, True)])
+def test_one_attention_workgroup_only_where_its_walk_is_short(lib, seq, B, nkv, d, one):
+    """Which batches' decode attention takes one workgroup per kv head (at most four splits): the
+    shapes whose steps were measured on both sides (the last fills the GPU with four splits)."""
+    f = lib._ZN3fpk17attn_decode_splitEiiiiPiS0_
+    f.restype = None
+    ns, kps = ctypes.c_int(), ctypes.c_int()
+    f(seq, B, nkv, d, ctypes.byref(ns), ctypes.byref(kps))
+    assert (ns.value <= 4) == one
+    assert kps.value % 32 == 0 and (ns.value - 1) * kps.value < seq <= ns.value * kps.value

@@ -479,12 +479,19 @@ def test_sp24_decode_batches(B, hidden, heads, head_dim, ffn):
     assert max(res.decode_errs) <= TOL
 
 
-# Decode attention without a merge kernel (a batch whose context is at most 16 blocks of 32
-# keys) and with one (17 blocks), grouped queries, at the last position of the cache.
-@pytest.mark.parametrize("seq", [33, 512, 513])
-def test_decode_attention_one_workgroup_edge(seq):
-    log(f"decode attention, cache of {seq} positions")
-    res = run_parity(Shape(1, 256, 4, 2, 64, 384, 3, seq - 2, seq), "bf16", "int8", 3, seq - 2, 2)
+# Decode attention without a merge kernel and with one, on both sides of the rule (the context in
+# blocks of 32 keys over four waves): head_dim 64 up to 16 blocks, 128 up to 8, 128 with at least
+# 96 workgroups up to 16; grouped queries, at the last position of the cache.
+ONE_WG_CASES = [(64, "int8", 3, 2, 33), (64, "int8", 3, 2, 512), (64, "int8", 3, 2, 513),
+                (128, "bf16", 3, 2, 256), (128, "int8", 3, 2, 257), (128, "bf16", 48, 2, 512),
+                (128, "bf16", 48, 2, 513)]
+
+
+@pytest.mark.parametrize("d,kvq,B,nkv,seq", ONE_WG_CASES)
+def test_decode_attention_one_workgroup_edge(d, kvq, B, nkv, seq):
+    log(f"decode attention, head_dim {d}, {kvq}, {B} sequences, {nkv} kv heads, cache of {seq} positions")
+    res = run_parity(Shape(1, 256, 2 * nkv, nkv, d, 384, B, seq - 2, seq), "bf16", kvq, B, seq - 2, 2,
+                     rows=sorted({0, B // 2, B - 1}))
     assert res.prefill_err <= TOL
     assert max(res.decode_errs) <= TOL
 
