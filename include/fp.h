@@ -178,8 +178,10 @@ fp_status fp_decode_step_noalloc(fp_layer* layer, const void* x, void* y, void* 
  * default) or launch the kernels one by one (0).  Results are identical.  Graphs are
  * captured on first use per (x, y, n, active batch) for fp_decode_steps; each cache holds
  * at most 16 graphs and is emptied (after a device synchronisation) when a new capture
- * would exceed that.  fp_decode_step always launches its kernels one by one (a graph per
- * single step takes longer); with 1 it refuses a stream that is being captured.
+ * would exceed that.  fp_decode_step launches its kernels one by one (a graph per single
+ * step takes longer), except that with 1 the inner layers of a fingerprint of many small
+ * layers are one graph, captured on the first step of each batch size and kept for every x
+ * and y (at most 16, likewise); with 1 it refuses a stream that is being captured.
  */
 fp_status fp_set_decode_graph(fp_layer* layer, int32_t enable);
 

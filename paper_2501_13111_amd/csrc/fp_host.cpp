@@ -197,6 +197,7 @@ struct fp_layer {
     std::map<std::tuple<void*, void*, int, int>, hipGraphExec_t> mgraphs;     // (x, y, n, B)
     // fp_generate's decode loop: (out_ids, logits, force_ids, n_out, B)
     std::map<std::tuple<int32_t*, float*, const int32_t*, int, int>, hipGraphExec_t> ggraphs;
+    std::map<int, hipGraphExec_t> sgraphs;   // inner layers of a single step, by batch (step_graph)
     Prof prof;
     size_t bytes_w = 0, bytes_kv = 0, bytes_ws = 0;
     std::vector<void*> allocs;
@@ -243,8 +244,16 @@ void drop_graphs(fp_layer* h) {
     h->ggraphs.clear();
 }
 
+void drop_step_graphs(fp_layer* h) {
+    if (h->sgraphs.empty()) return;
+    (void)hipDeviceSynchronize();
+    for (auto& kv : h->sgraphs) (void)hipGraphExecDestroy(kv.second);
+    h->sgraphs.clear();
+}
+
 void free_all(fp_layer* h) {
     drop_graphs(h);
+    drop_step_graphs(h);
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
     h->cap_stream = nullptr;
     for (void* p : h->allocs) (void)hipFree(p);
@@ -730,13 +739,13 @@ AttnDecArgs attn_args(fp_layer* h, int l, int ks, int B, float* dump) {
 // their inputs (layer 0 sums the squares of its input row itself), attention rotates
 // and appends the new K / V itself, and a light kernel per residual add reduces the
 // split-K partials and the row's sum of squares.
-fp_status enqueue_decode_single(fp_layer* h, const uint16_t* x, uint16_t* y, hipStream_t st) {
+fp_status enqueue_decode_single(fp_layer* h, const uint16_t* x, uint16_t* y, hipStream_t st, int l_beg, int l_end) {
     const fp_shape& s = h->s;
     const int B = h->B;
     const int ssq_blocks = resid_ssq_blocks(s.hidden);
     fp_status rc;
     int ks;
-    for (int l = 0; l < s.n_layers; ++l) {
+    for (int l = l_beg; l < l_end; ++l) {
         const LayerW& W = h->L[l];
         const uint16_t* in = (l == 0) ? x : h->xbuf;
         uint16_t* out = (l == s.n_layers - 1) ? y : h->xbuf;
@@ -794,17 +803,18 @@ fp_status enqueue_decode_single(fp_layer* h, const uint16_t* x, uint16_t* y, hip
 // whose input is the previous step's output (chained: n steps in one call) starts from that
 // (the same kernel computes it from the same bf16 row, so the result is bit for bit the one
 // the step's own first RMSNorm would give).
-fp_status enqueue_decode_batch(fp_layer* h, const uint16_t* x, uint16_t* y, hipStream_t st, bool chained) {
+fp_status enqueue_decode_batch(fp_layer* h, const uint16_t* x, uint16_t* y, hipStream_t st, bool chained, int l_beg,
+                               int l_end) {
     const fp_shape& s = h->s;
     const int B = h->B;
     fp_status rc;
     int ks;
-    if (!chained) {
+    if (l_beg == 0 && !chained) {
         h->prof.mark(FP_K_RMSNORM, 0);
         HIPCHK(launch_resid_norm(nullptr, 0, B, s.hidden, x, nullptr, h->L[0].attn_norm, s.rms_eps, h->act_in,
                                  h->act_fmt, h->ssq, nullptr, st));
     }
-    for (int l = 0; l < s.n_layers; ++l) {
+    for (int l = l_beg; l < l_end; ++l) {
         const LayerW& W = h->L[l];
         const uint16_t* in = (l == 0) ? x : h->xbuf;
         uint16_t* out = (l == s.n_layers - 1) ? y : h->xbuf;
@@ -837,9 +847,45 @@ fp_status enqueue_decode_batch(fp_layer* h, const uint16_t* x, uint16_t* y, hipS
 
 // 2:4 sparse weights run every batch size, one sequence included, on the batch schedule
 // (their projection kernel stages plain activations).
+bool single_schedule(const fp_layer* h, int B) { return B == 1 && h->wq != FP_WQ_BF16_2OF4; }
+
+// Layers l_beg .. l_end - 1 of one step: layer 0 reads x, the last one writes y.
+fp_status enqueue_decode_layers(fp_layer* h, const uint16_t* x, uint16_t* y, hipStream_t st, bool chained, int l_beg,
+                                int l_end) {
+    return single_schedule(h, h->B) ? enqueue_decode_single(h, x, y, st, l_beg, l_end)
+                                    : enqueue_decode_batch(h, x, y, st, chained, l_beg, l_end);
+}
+
 fp_status enqueue_decode(fp_layer* h, const uint16_t* x, uint16_t* y, hipStream_t st, bool chained = false) {
-    return h->B == 1 && h->wq != FP_WQ_BF16_2OF4 ? enqueue_decode_single(h, x, y, st)
-                                                 : enqueue_decode_batch(h, x, y, st, chained);
+    return enqueue_decode_layers(h, x, y, st, chained, 0, h->s.n_layers);
+}
+
+// The inner layers of a single step (all but the first and the last) as one graph, captured
+// on the active batch's first use: *out.  They read and write the handle's own buffers only,
+// so one graph serves every x and y, and stays valid when the batch changes and returns.
+fp_status step_graph(fp_layer* h, hipGraphExec_t* out) {
+    const auto it = h->sgraphs.find(h->B);
+    if (it != h->sgraphs.end()) {
+        *out = it->second;
+        return FP_OK;
+    }
+    if (h->sgraphs.size() >= GRAPH_CACHE_MAX) drop_step_graphs(h);
+    hipGraph_t g = nullptr;
+    hipGraphExec_t ge = nullptr;
+    HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
+    const fp_status rc = enqueue_decode_layers(h, nullptr, nullptr, h->cap_stream, false, 1, h->s.n_layers - 1);
+    hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
+    if (rc) {
+        if (g) (void)hipGraphDestroy(g);
+        return rc;
+    }
+    if (e != hipSuccess) return fail(FP_ERR_HIP, "graph capture failed: %s", hipGetErrorString(e));
+    e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(g);
+    if (e != hipSuccess) return fail(FP_ERR_HIP, "graph instantiate failed: %s", hipGetErrorString(e));
+    h->sgraphs.emplace(h->B, ge);
+    *out = ge;
+    return FP_OK;
 }
 
 // Final RMSNorm, LM head and greedy argmax of position T - 1 of each of B sequences of
@@ -893,7 +939,29 @@ void decode_scratch_floats(const fp_layer* h, int B, size_t* part, size_t* part2
     *ssq = (size_t)B * resid_ssq_blocks(s.hidden);
 }
 
+size_t layer_weight_bytes(const fp_layer* h) {
+    size_t n = 0;
+    for (const Mat* m : {&h->L[0].qkv, &h->L[0].o, &h->L[0].gu, &h->L[0].down}) n += (size_t)m->N * m->K;
+    return h->wq == FP_WQ_INT4_G128 ? n / 2 : h->wq == FP_WQ_INT8_CHANNEL ? n : h->wq == FP_WQ_BF16_2OF4 ? n + n / 8 : 2 * n;
+}
+
 }  // namespace
+
+// A launch takes the host 3.3 to 3.8 us (26 us for a layer of one sequence, 28 for one of a batch),
+// so a layer whose kernels are shorter is bound by its launches, while a graph leaves the GPU idle
+// for about 4 us once per step.  Layers that short have few weights; from eight layers on the
+// graph's start is less than the launches it saves, and its capture, once per batch, is repaid
+// within some 30 steps.  Step in us, launched / inner layers as a graph, int8 weights, 32 steps
+// of 64 positions and more.  One sequence: hidden 256, 4 / 6 / 8 / 32 layers 103.8 106.2 / 156.1
+// 155.0 / 204.4 200.3 / 829 775; 1024 (13 MB a layer), 8 / 32 layers 227.6 222.0 / 919 869; 1536
+// (26 MB) 251.9 250.6 / 1020 988; 4096 (202 MB), 4 layers 254.1 257.2.  7 sequences: 256 (0.8 MB),
+// 8 / 32 layers 231.2 226.1 / 945 916; 512 (3.2 MB) 243.2 238.8 / 1006 1003; 1024 266.3 269.8 /
+// 1068 1069; 1536 301.0 303.4 / 1201 1202.  A caller that waits for every step has no launches
+// ahead, so there the graph gains more: 7 sequences, 1536, 32 layers 1379 1226, 8 layers 344 323.
+bool fpk::decode_step_inner_graph(int n_layers, bool single, size_t layer_bytes) {
+    const int from = single || layer_bytes <= (size_t)4 << 20 ? 8 : 16;
+    return n_layers >= from && layer_bytes <= (size_t)32 << 20;
+}
 
 // One decode step, launched kernel by kernel (no graph capture, no allocation), with its
 // scratch buffers carved from the caller-provided device region [scratch, scratch + bytes)
@@ -1237,16 +1305,26 @@ fp_status fp_decode_step(fp_layer* h, const void* x, void* y, void* stream) {
     if (!h->unbacked) {
         hipStream_t st = (hipStream_t)stream;
         fp_status rc;
-        // One step is launched kernel by kernel: its launches (2.5 us each on the host) run ahead
-        // of its kernels, while a graph launch per step left the GPU idle for about 4 us between
-        // steps (tiny fingerprint, 16 calls after a prefill: 512 us with a graph per step, 452
-        // without; a grouped-query layer, 7 sequences, 9 calls: 660 and 606).  With the decode
-        // graph on, a stream under capture is refused, as replaying a graph into it was.
+        const int nl = h->s.n_layers;
+        // With the decode graph on, a stream under capture is refused, as replaying a graph into
+        // it would be.  A step is launched kernel by kernel: a graph of the whole step leaves the
+        // GPU idle for about 4 us per step (7B int8 layer, one sequence, 63.8 us launched, 67.2 as
+        // a graph).  Where the launches themselves are the bound, the inner layers are one graph:
+        // the first layer's kernels cover its start.
         if (h->use_graph && !h->dump && !h->ldump) {
             hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
             HIPCHK(hipStreamIsCapturing(st, &cs));
             if (cs != hipStreamCaptureStatusNone)
                 return fail(FP_ERR_HIP, "decode step on a capturing stream with the decode graph on");
+            if (decode_step_inner_graph(nl, single_schedule(h, h->B), layer_weight_bytes(h))) {
+                hipGraphExec_t ge = nullptr;
+                if ((rc = step_graph(h, &ge))) return rc;
+                if ((rc = enqueue_decode_layers(h, (const uint16_t*)x, (uint16_t*)y, st, false, 0, 1))) return rc;
+                HIPCHK(hipGraphLaunch(ge, st));
+                if ((rc = enqueue_decode_layers(h, (const uint16_t*)x, (uint16_t*)y, st, false, nl - 1, nl))) return rc;
+                h->pos += 1;
+                return FP_OK;
+            }
         }
         if ((rc = enqueue_decode(h, (const uint16_t*)x, (uint16_t*)y, st))) return rc;
     }

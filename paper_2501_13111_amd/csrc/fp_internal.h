@@ -259,6 +259,9 @@ int head_logit_blocks(int V);
 hipError_t launch_logits_argmax(const float* part, int ks, int B, int V, float* logits, float* bval, int* bidx,
                                 int* out_ids, hipStream_t st);
 
+// Whether a single decode step launches its inner layers as one graph.
+bool decode_step_inner_graph(int n_layers, bool single, size_t layer_bytes);
+
 // Host runtime hooks for the allocation-free decode step (noalloc.hip): one eager decode
 // step whose scratch buffers live in [scratch, scratch + bytes), and setting the
 // thread's last-error message.

@@ -327,3 +327,15 @@ def test_one_attention_workgroup_only_where_its_walk_is_short(lib, seq, B, nkv, 
     f(seq, B, nkv, d, ctypes.byref(ns), ctypes.byref(kps))
     assert (ns.value <= 4) == one
     assert kps.value % 32 == 0 and (ns.value - 1) * kps.value < seq <= ns.value * kps.value
+
+
+@pytest.mark.parametrize("layers,single,mbytes,graph", [
+    (1, True, 0.8, False), (4, True, 0.8, False), (7, True, 0.8, False), (8, True, 0.8, True), (32, True, 26, True),
+    (32, True, 202, False), (8, False, 0.8, True), (32, False, 3.2, True), (8, False, 13, False), (32, False, 26, True),
+    (4, False, 0.8, False)])
+def test_single_steps_use_a_graph_only_where_launches_bound_them(lib, layers, single, mbytes, graph):
+    """Whether fp_decode_step launches its inner layers as one graph: the shapes whose steps were
+    measured both ways."""
+    f = lib._ZN3fpk23decode_step_inner_graphEibm
+    f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int, ctypes.c_bool, ctypes.c_size_t]
+    assert f(layers, single, int(mbytes * 1e6)) == graph

@@ -166,6 +166,40 @@ def test_graph_replay_matches_eager():
     assert torch.equal(outs[False].view(torch.int16), outs[True].view(torch.int16))
 
 
+@pytest.mark.parametrize("wq,kvq", [("int8", "bf16"), ("bf16", "int8"), ("sp24", "bf16")])
+def test_single_steps_with_inner_layers_as_a_graph(wq, kvq):
+    """Eight small layers: fp_decode_step launches layers 1 .. 6 as one graph per batch, which
+    serves every x and y and outlives a prefill of another batch.  Bit for bit the steps launched
+    one by one, to the cache's capacity, also where single and multiple steps take turns."""
+    import torch
+    from paper_2501_13111_amd import Fingerprint, fill_normal
+    P, n = 20, 9
+    outs = {}
+    for graph in (False, True):
+        with Fingerprint(Shape(8, 256, 4, 2, 64, 384, 3, P, P + n), wq, kvq, seed=4) as fp:
+            fp.set_decode_graph(graph)
+            res = []
+            for B in (3, 1, 2, 3, 1):
+                log(f"inner-layer graph {wq} graph={graph} B={B}")
+                x = torch.empty(B * P * 256, dtype=torch.bfloat16, device="cuda")
+                fill_normal(x, 4 + len(res), -1, 15, 0.0, 1.0)
+                y = torch.empty_like(x)
+                fp.prefill(x, y, B, P)
+                a = y.view(B, P, 256)[:, -1, :].contiguous()
+                for s in range(n - 2):
+                    b = torch.empty_like(a)             # a new output buffer for every step
+                    fp.decode_step(a, b)
+                    res.append(b.clone())
+                    a = b
+                    if s == 3:
+                        fp.decode_steps(a, torch.empty_like(a), 2)
+                        res.append(a.clone())
+            torch.cuda.synchronize()
+            outs[graph] = [t.view(torch.int16).cpu() for t in res]
+    assert len(outs[True]) == len(outs[False]) == 5 * (n - 1)
+    assert all(torch.equal(u, v) for u, v in zip(outs[False], outs[True]))
+
+
 @pytest.mark.parametrize("B,wq,kvq", [(3, "int4", "int8"), (1, "bf16", "bf16"), (1, "int8", "int8")],
                          ids=["batch3-int4-int8kv", "single-bf16", "single-int8-int8kv"])
 def test_decode_steps_match_single_steps(B, wq, kvq):
