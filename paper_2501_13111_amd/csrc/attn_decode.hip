@@ -114,12 +114,17 @@ __device__ __forceinline__ int qdim(int j, int g) {
 template <int D, bool KV8>
 struct DecChunk {
     static constexpr int NK = KV8 ? D / 64 : D / 32;   // 16-byte K loads per key tile
-    // chunks in flight per wave.  bf16 caches: one, and three workgroups per CU instead of two (143
-    // registers instead of 187): their queries' and appends' round trips cover each other
-    // (13B step at 32 sequences of 144 positions 99.1 -> 95.7 us, of 1008 positions 211.8 ->
-    // 208.9).  int8 caches, whose chunks are half the bytes: two (7B int8 step 83.2 us, 87.1 with
-    // one); three or four are no faster.
-    static constexpr int PD = KV8 ? 2 : 1;
+    // Chunks in flight per wave.  bf16 caches of head_dim 128: one, and three workgroups per CU
+    // instead of two (143 registers instead of 187): their queries' and appends' round trips cover
+    // each other.  Step of a layer with a narrow MLP (ffn 128), us, two / one: 40 kv heads, 32
+    // sequences, contexts of 136 / 520 / 1000 positions 72.1 68.0 / 118.8 121.2 / 181.2 176.4; 32 kv
+    // heads, 64 sequences, 136 / 520 87.7 83.4 / 169.4 170.3, 16 sequences, 1016 / 2040 83.1 82.0 /
+    // 138.5 139.9; 8 sequences or fewer within 1%.  So short contexts gain up to 6%, longer ones
+    // lie between 3% better and 2% worse, with no line that the shape draws.  head_dim 64, whose
+    // chunks are half the bytes: two (4 kv heads, 32 sequences, 2040 positions 43.0, 45.9 with
+    // one; 6 kv heads, 32 sequences 66.4 and 69.5, 64 sequences of 1016 70.1 and 71.8).  int8
+    // caches likewise (7B int8 step 83.2, 87.1 with one); three or four are no faster.
+    static constexpr int PD = KV8 || D == 64 ? 2 : 1;
     u32x4 k[2][NK];
     typename std::conditional<KV8, u32x2, u32x4>::type v[D / 16];   // int8: 8 codes; bf16: 8 values
     u32x2 ks[2], vs[2];                                 // int8: fp16 scales of keys 16 t + 4 g + i

@@ -516,8 +516,9 @@ def test_sp24_decode_batches(B, hidden, heads, head_dim, ffn):
 # Decode attention without a merge kernel and with one, on both sides of the rule (the context in
 # blocks of 32 keys over four waves): head_dim 64 up to 16 blocks, 128 up to 8, 128 with at least
 # 96 workgroups up to 16; grouped queries, at the last position of the cache.
-ONE_WG_CASES = [(64, "int8", 3, 2, 33), (64, "int8", 3, 2, 512), (64, "int8", 3, 2, 513),
-                (128, "bf16", 3, 2, 256), (128, "int8", 3, 2, 257), (128, "bf16", 48, 2, 512),
+# bf16 head_dim 64 also with waves of seven chunks (two in flight), the last one of two.
+ONE_WG_CASES = [(64, "int8", 3, 2, 33), (64, "int8", 3, 2, 512), (64, "int8", 3, 2, 513), (64, "bf16", 3, 2, 512),
+                (64, "bf16", 3, 2, 513), (64, "bf16", 24, 8, 1184), (128, "bf16", 3, 2, 256), (128, "int8", 3, 2, 257), (128, "bf16", 48, 2, 512),
                 (128, "bf16", 48, 2, 513)]
 
 
