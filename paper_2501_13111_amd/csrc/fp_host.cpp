@@ -1079,11 +1079,11 @@ fp_status alloc_storage(fp_layer* h) {
     if ((st = alloc_t(h, &h->part2, (size_t)KSMAX * s.max_batch * 2 * F, &h->bytes_ws))) return st;
     {
         // the largest split-K partial buffer any prefill size up to Mmax asks for.  From 256 rows
-        // on, the factors never fall as rows are added within a 256-row tile (gemm.hip), so the
-        // worst case of a tile is its last row; below one tile every row count is asked
+        // on, the factors depend on whole groups of 64 rows (gemm.hip), so the worst case of a
+        // group is its last row; below, every row count is asked
         size_t pp = 0;
         const int Mp = (int)act_elems(h);
-        for (int M = std::min(2, Mp); M > 0; M = M == Mp ? 0 : M < 256 ? M + 1 : std::min(M + 256, Mp)) {
+        for (int M = std::min(2, Mp); M > 0; M = M == Mp ? 0 : M < 256 ? M + 1 : std::min(M + 64, Mp)) {
             int kr;
             const int kq = gemm_qkv_split_factor(M, h->nqkv, H, h->wq, &kr);
             const int ko = prefill_split(h, M, H, h->q_dim, 0, &kr);

@@ -1012,20 +1012,42 @@ int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange) {
     if (ks > GEMM_SPLIT_MAX) ks = GEMM_SPLIT_MAX;
     if (ks > stages / 4) ks = stages / 4;
     if (ks < 2) return 1;
+    const int ncols = dual_F > 0 ? 2 * dual_F : N;
     if (M >= BT) {
-        // Fewer partials where writing and reading them costs more than the shorter k ranges save
-        // (in us, the model of gemm_qkv_split_factor).  4096 x 4096 with its reduction at 512 rows:
-        // 8 partials 42 to 47, 4 partials 42; a bf16 layer of hidden 4096, 512 rows: 320 -> 316.
-        const double mb = 4e-6 * ((M + BT - 1) / BT) * BT * (dual_F > 0 ? 2.0 * dual_F : N);
-        double best = 1e30;
-        for (int k = 2, kmax = ks; k <= kmax; ++k) {
+        // The cheapest of one partial (no split: the small tiling, or the large one from its
+        // threshold on) and 2 .. ks, in us.  Fitted to 256 to 2048 rows of eight layers of hidden
+        // 512 to 8192 in every format, each factor measured with its reduction (split GEMM within
+        // 10% rms, small tiling 7 to 10%), and to whole prefills, which make a partial dearer than
+        // its own kernels do (0.27 us per MB instead of 0.19).  Chosen by it those phases take 31.0
+        // ms together, 30.8 with the best factor of each, 32.1 with the partials' traffic weighed
+        // against the k range alone; prefills of 100 to 4000 tokens of these shapes 3.3% less (8.7%
+        // less than with as many partials as fit).  One partial / two, us: [gate; up] 5632 x 1024
+        // 256 rows 14.5 / 27.6, 1024 rows 24.7 / 45.2 (88 large tiles); 16384 x 3072 512 rows 66.6 /
+        // 87.0 (128); 8192 x 1024 1024 rows with its residual 38.5 / 54.2.  Not the fewest either:
+        // 5120 x 5120 256 rows, 5 / 8 / 12 partials 48.7 / 43.2 / 43.2.  Row counts go by whole 64,
+        // as the workgroups of the small tiling do; the partial buffer is sized by that.
+        const int m64 = (M + 63) / 64;
+        const double u = K / 64.0, mb = 4e-6 * 64 * m64 * ncols;      // one partial
+        const int tn = dual_F > 0 ? (dual_F + 63) / 64 : (N + GBN - 1) / GBN;
+        const int t64 = tn * m64, t128 = tn * ((M + 127) / 128);
+        double best = tiles >= GEMM_BIG_MIN_TILES ? 13.0 + u * (0.65 + 0.72 * tiles / 256)
+                      : t128 < GEMM_SMALL_TILES   ? 7.0 + u * (0.54 + 0.37 * std::max(0.0, t64 / 256.0 - 1.0))
+                                                  : 10.7 + u * (0.73 + 0.5 * (t128 / 256.0 - 1.0));
+        if (dual_F <= 0) best += 8.0 + 0.2 * mb;                      // the residual, and an RMSNorm after it
+        const double wmb = 1e-6 * N * K * (wf == W_BF16 ? 2.0 : wf == W_INT8 ? 1.0 : 0.5);   // weights, from memory
+        int pick = 1;
+        for (int k = 2; k <= ks; ++k) {
             const int per = (stages + k - 1) / k, n = (stages + per - 1) / per;
-            const double t = 1.1 * per * tk / 64 + (0.17 + 0.25) * n * mb;
+            const double t = std::max(8.2 + 1.15 * per * tk / 64, wmb / 3.3 + 0.4 * per * tk / 64) + 0.27 * n * mb +
+                             0.2 * std::max(0.0, n * mb - 48.0) +
+                             (dual_F > 0 ? 2.6 + 0.77 * mb + 0.012 * n * mb : 3.6 + 0.25 * mb + 0.09 * n * mb);
             if (t < best) {
                 best = t;
-                ks = n;
+                pick = n;
             }
         }
+        if (pick < 2) return 1;
+        ks = pick;
     }
     const int per = (stages + ks - 1) / ks;
     if (M < BT) {
@@ -1034,7 +1056,6 @@ int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange) {
         // reduction and its partials' traffic.  In us, fitted to 8 to 255 rows of K 1024 to
         // 11008: e.g. 100 rows, int4 4096 x 11008 102 -> 31 (with the norm), 7168 x 8192 SwiGLU
         // 74 -> 32; but 22016 x 4096 SwiGLU on 172 workgroups either way 39 -> 43 at 8 rows.
-        const int ncols = dual_F > 0 ? 2 * dual_F : N;
         const int small = ((M + 63) / 64) * (dual_F > 0 ? (dual_F + 63) / 64 : (N + GBN - 1) / GBN);
         const double t_small = 3.0 + 0.57 * K / 64 + (dual_F > 0 ? 0.0 : 4.0);
         const double t_split = 12.0 + 1.05 * per * tk / 64 + 0.42e-6 * 4.0 * ks * M * ncols;
@@ -1054,8 +1075,7 @@ int gemm_split_factor(int M, int N, int K, int dual_F, int wf, int* krange) {
 // int8 10240 x 8192 512 rows 125 / 73.4, 1280 x 8192 67.5 / 23.1; but 768 x 768 10.0 / 11.8
 // and 3072 x 2048 21.0 / 19.1 before the reads.  Int4 stays on the small tiling: the large one
 // has no partials in the exact int4 scheme that it uses for this projection.
-// Within a 256-row tile the factor never falls as rows are added: the small tiling's time (w)
-// grows and the split's does not depend on the rows.  The partial buffer is sized by that.
+// The factor depends on whole 64 rows (w) and 256-row tiles; the partial buffer is sized by that.
 int gemm_qkv_split_factor(int M, int N, int K, int wf, int* krange) {
     const int rows = (M + BT - 1) / BT, tiles = rows * ((N + BT - 1) / BT);
     const int tk = big_tk(wf);

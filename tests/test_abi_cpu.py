@@ -291,7 +291,7 @@ def test_estimators_agree_with_the_oracle():
 
 def test_split_partials_never_exceed_the_probed_row_counts(lib):
     """The split-K partial buffer of the prefill is sized over the row counts 2 .. 256 and then
-    over whole 256-row tiles and the largest prefill; every row count between them needs no more."""
+    over whole groups of 64 rows and the largest prefill; every row count between them needs no more."""
     plain = lib._ZN3fpk17gemm_split_factorEiiiiiPi
     qkv = lib._ZN3fpk21gemm_qkv_split_factorEiiiiPi
     for f in (plain, qkv):
@@ -308,7 +308,7 @@ def test_split_partials_never_exceed_the_probed_row_counts(lib):
                          lambda M: plain(M, 2 * N, k, N, wf, ctypes.byref(kr)) * M):
                 for last in (rng.randint(257, 1500), 1024):
                     split = lambda M: need(M) if need(M) > M else 0
-                    probes = [*range(2, 257), *range(512, last, 256), last]
+                    probes = [*range(2, 257), *range(320, last, 64), last]
                     cap = max(split(M) for M in probes)
                     assert all(split(M) <= cap for M in range(257, last + 1)), (N, K, wf, last)
 
@@ -339,3 +339,24 @@ def test_single_steps_use_a_graph_only_where_launches_bound_them(lib, layers, si
     f = lib._ZN3fpk23decode_step_inner_graphEibm
     f.restype, f.argtypes = ctypes.c_bool, [ctypes.c_int, ctypes.c_bool, ctypes.c_size_t]
     assert f(layers, single, int(mbytes * 1e6)) == graph
+
+
+def _split(lib, M, N, K, F, wf):
+    f = lib._ZN3fpk17gemm_split_factorEiiiiiPi
+    f.restype = ctypes.c_int
+    kr = ctypes.c_int()
+    n = f(M, N, K, F, wf, ctypes.byref(kr))
+    assert n == 1 or (n - 1) * kr.value < K <= n * kr.value and kr.value % (128 if wf == 2 else 64) == 0
+    return n
+
+
+@pytest.mark.parametrize("M,N,K,F,wf,lo,hi", [
+    # one partial is the cheapest by 10 us and more: [gate; up] of hidden 1024, 1536 and 3072, also
+    # where the large tiling runs unsplit (128 tiles)
+    (256, 5632, 1024, 2816, 1, 1, 1), (1024, 5632, 1024, 2816, 0, 1, 1), (300, 8448, 1536, 4224, 2, 1, 1),
+    (512, 16384, 3072, 8192, 0, 1, 1), (1024, 8192, 1024, 0, 2, 1, 1), (256, 27648, 5120, 13824, 0, 1, 1),
+    # long k ranges on few tiles: within 3 us of the best factor
+    (256, 5120, 5120, 0, 0, 7, 12), (300, 1024, 2816, 0, 1, 9, 11), (512, 3072, 8192, 0, 1, 8, 10),
+    (512, 4096, 11008, 0, 2, 6, 8)])
+def test_split_factor_of_measured_shapes(lib, M, N, K, F, wf, lo, hi):
+    assert lo <= _split(lib, M, N, K, F, wf) <= hi

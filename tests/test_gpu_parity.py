@@ -112,7 +112,7 @@ CASES = [
     # decode that ends exactly at the cache capacity (P + S = max_seq)
     ("full-capacity-int8", Shape(1, 256, 2, 2, 128, 384, 3, 29, 32), "int8", "int8", 3, 29, 3),
     ("batch33-int8-wide", Shape(1, 3584, 28, 28, 128, 512, 33, 8, 11), "int8", "int8", 33, 8, 3),
-    # prefill GEMMs with too few 256 x 256 tiles run split-K with reduction kernels
+    # prefill GEMMs with too few 256 x 256 tiles: o and down run split-K with reduction kernels
     # (M >= 256; M = 300 leaves a ragged row tile)
     ("splitk-bf16", Shape(2, 512, 4, 4, 128, 1024, 2, 160, 164), "bf16", "bf16", 2, 160, 2),
     ("splitk-int4-int8kv", Shape(2, 1024, 8, 8, 128, 2048, 2, 160, 164), "int4", "int8", 2, 160, 2),
@@ -587,6 +587,33 @@ def test_parity_small_prompt_split(case):
     log(f"case {name}: {shape} {wq}/{kvq} B={B} P={P}")
     res = run_parity(shape, wq, kvq, B, P, 1, layerwise=True)
     _report(name, res)
+    assert res.prefill_err <= TOL
+    assert all(e <= TOL for e in res.layer_errs)
+    assert max(res.decode_errs) <= TOL
+
+
+# From 256 rows on the number of partials is the cheapest of a model, one included: o and [gate; up]
+# split (hidden 2048, ffn 512; 257 rows and 3 x 100), and down split but [gate; up] not (hidden 512,
+# ffn 2048), in every format; ``want`` says which of o, [gate; up] and down are split.
+LARGE_SPLIT_CASES = [(wq, kvq, H, F, B, P, want)
+                     for wq, kvq in (("bf16", "bf16"), ("int8", "int8"), ("int4", "bf16"))
+                     for H, F, B, P, want in ((2048, 512, 1, 257, (1, 1, None)), (2048, 512, 3, 100, (1, 1, None)),
+                                              (512, 2048, 1, 300, (None, 0, 1)))]
+
+
+@pytest.mark.parametrize("wq,kvq,H,F,B,P,want", LARGE_SPLIT_CASES)
+def test_parity_large_prompt_split(wq, kvq, H, F, B, P, want):
+    import ctypes
+    import paper_2501_13111_amd as fpk
+    log(f"split from 256 rows on: {wq}/{kvq} hidden {H} ffn {F} {B} x {P}")
+    factor = fpk.load()._ZN3fpk17gemm_split_factorEiiiiiPi
+    factor.restype = ctypes.c_int
+    kr, wf = ctypes.c_int(), {"bf16": 0, "int8": 1, "int4": 2}[wq]
+    got = [factor(B * P, n, k, dual, wf, ctypes.byref(kr)) for n, k, dual in ((H, H, 0), (2 * F, H, F), (H, F, 0))]
+    assert all(w is None or (g > 1) == bool(w) for g, w in zip(got, want)), got
+    res = run_parity(Shape(2, H, H // 128, 2, 128, F, B, P, P + 2), wq, kvq, B, P, 1, layerwise=True,
+                     rows=sorted({0, B - 1}))
+    _report(f"large-split-{wq}-{H}", res)
     assert res.prefill_err <= TOL
     assert all(e <= TOL for e in res.layer_errs)
     assert max(res.decode_errs) <= TOL
