@@ -56,8 +56,7 @@ __device__ __forceinline__ void append_kv(const AttnDecArgs& a, int b, int kvh, 
         float sum[4];
         sum_parts_cols<4>(cols, a.ks, pstride, sum);
         const float u = sum[0], x = sum[1];
-        k0 = __fsub_rn(__fmul_rn(u, c), __fmul_rn(x, sn));
-        k1 = __fadd_rn(__fmul_rn(x, c), __fmul_rn(u, sn));
+        rotate_pair(u, x, c, sn, k0, k1);
         v0 = sum[2];
         v1 = sum[3];
         if (a.dump) {   // [2, B, nkv, D] pre-quantisation K, V
@@ -220,8 +219,10 @@ __global__ void __launch_bounds__(256, 2) attn_decode_kernel(AttnDecArgs a, int 
         auto rotate = [&](int i, float u, float v) {
             const int c = i / (D / 2), j = i % (D / 2);
             const float cs = a.cos_t[(int64_t)pos * (D / 2) + j], sn = a.sin_t[(int64_t)pos * (D / 2) + j];
-            qs[c * D + j] = act_store(__fsub_rn(__fmul_rn(u, cs), __fmul_rn(v, sn)), AF);
-            qs[c * D + j + D / 2] = act_store(__fadd_rn(__fmul_rn(v, cs), __fmul_rn(u, sn)), AF);
+            float lo, hi;
+            rotate_pair(u, v, cs, sn, lo, hi);
+            qs[c * D + j] = act_store(lo, AF);
+            qs[c * D + j + D / 2] = act_store(hi, AF);
         };
         if (npairs <= 256) {
             if (i0 < npairs) rotate(i0, qsum[0], qsum[1]);

@@ -36,6 +36,38 @@ __device__ __forceinline__ uint32_t pack_f16_hw(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// Rotary embedding of the pair (u, v) by its cosine and sine: one product rounded, the other
+// fused with the sum.  Every kernel that rotates calls this, so queries and cached keys are the
+// same bits whichever of them a prompt or a step takes.
+__device__ __forceinline__ void rotate_pair(float u, float v, float c, float s, float& lo, float& hi) {
+    lo = fmaf(u, c, -(v * s));
+    hi = fmaf(v, c, u * s);
+}
+// fp16 of a0 b0 + c0 (low half) and a1 b1 + c1, each rounded once.  In asm: the compiler fuses the
+// conversion into the sum or not by what else uses the sum, and the bits differ.
+__device__ __forceinline__ uint32_t fma_f16x2(float a0, float b0, float c0, float a1, float b1, float c1) {
+    uint32_t d;
+    asm("v_fma_mixlo_f16 %0, %1, %2, %3\n\ts_nop 0\n\tv_fma_mixhi_f16 %0, %4, %5, %6\n\ts_nop 0"
+        : "=&v"(d) : "v"(a0), "v"(b0), "v"(c0), "v"(a1), "v"(b1), "v"(c1));
+    return d;
+}
+// Two neighbouring pairs of a query in the prefill attention's operand format (lo, hi: two values
+// each): fp16 or bf16.
+template <bool F16>
+__device__ __forceinline__ void rotate_query(float u0, float u1, float v0, float v1, float c0, float c1, float s0,
+                                             float s1, uint32_t& lo, uint32_t& hi) {
+    if constexpr (F16) {
+        lo = fma_f16x2(u0, c0, -(v0 * s0), u1, c1, -(v1 * s1));
+        hi = fma_f16x2(v0, c0, u0 * s0, v1, c1, u1 * s1);
+    } else {
+        float l0, l1, h0, h1;
+        rotate_pair(u0, v0, c0, s0, l0, h0);
+        rotate_pair(u1, v1, c1, s1, l1, h1);
+        lo = pack_bf16_hw(l0, l1);
+        hi = pack_bf16_hw(h0, h1);
+    }
+}
+
 __device__ __forceinline__ uint16_t f2h(float f) {
     _Float16 h = (_Float16)f;                      // v_cvt_f16_f32, round to nearest even
     return __builtin_bit_cast(uint16_t, h);

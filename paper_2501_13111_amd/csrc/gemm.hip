@@ -431,18 +431,6 @@ __device__ __forceinline__ u32x4 i4x8_to_f16x8_q(uint32_t w, f16x2 b1024, f16x2 
 // 128 tokens m .. m + 127, all in whole 32-position blocks; scl: 128 x 4 floats.  The
 // arithmetic and the rounding are those of rope_q_kernel and kv_append_kernel (rows.hip).
 constexpr int ROPE_RS = 260;      // floats: the accumulators' rows 4 apart are 16 banks apart
-// fp16 queries: product, fused second product and the rounding to fp16 in two instructions
-// (outside the contract(off) region, like the same expression in rope_q_kernel)
-__device__ __forceinline__ void rot_f16x4(const f32x4& u, const f32x4& v, const f32x4& c, const f32x4& s, u32x2& lo, u32x2& hi) {
-    f32x4 a, b;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        a[e] = __fsub_rn(__fmul_rn(u[e], c[e]), __fmul_rn(v[e], s[e]));
-        b[e] = __fadd_rn(__fmul_rn(v[e], c[e]), __fmul_rn(u[e], s[e]));
-    }
-    lo = u32x2{pack_f16_hw(a[0], a[1]), pack_f16_hw(a[2], a[3])};
-    hi = u32x2{pack_f16_hw(b[0], b[1]), pack_f16_hw(b[2], b[3])};
-}
 #pragma clang fp contract(off)
 template <int D>
 __device__ __forceinline__ void rope_store(const RopeKvArgs& ro, const float* st, float* scl, int m, int head0) {
@@ -474,18 +462,25 @@ __device__ __forceinline__ void rope_store(const RopeKvArgs& ro, const float* st
             if (h >= ro.nh + 2 * ro.nkv) break;
             const f32x4 u = *(const f32x4*)(st + row * ROPE_RS + hh * D + 4 * l);
             const f32x4 v = *(const f32x4*)(st + row * ROPE_RS + hh * D + HALF + 4 * l);
-            // as those kernels' arithmetic is compiled: one product rounded, the other fused
             f32x4 lo, hi;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                lo[e] = fmaf(u[e], c[e], -(v[e] * s[e]));
-                hi[e] = fmaf(v[e], c[e], u[e] * s[e]);
+                float le, he;
+                rotate_pair(u[e], v[e], c[e], s[e], le, he);
+                lo[e] = le;
+                hi[e] = he;
             }
             if (h < ro.nh) {
                 uint16_t* q = ro.qout + (((int64_t)b * ro.nh + h) * ro.T + pos) * D + 4 * l;
-                u32x2 ql = u32x2{pack_bf16_hw(lo[0], lo[1]), pack_bf16_hw(lo[2], lo[3])};
-                u32x2 qh = u32x2{pack_bf16_hw(hi[0], hi[1]), pack_bf16_hw(hi[2], hi[3])};
-                if (ro.kv_int8) rot_f16x4(u, v, c, s, ql, qh);
+                u32x2 ql, qh;
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    uint32_t a, b2;
+                    if (ro.kv_int8) rotate_query<true>(u[e], u[e + 1], v[e], v[e + 1], c[e], c[e + 1], s[e], s[e + 1], a, b2);
+                    else rotate_query<false>(u[e], u[e + 1], v[e], v[e + 1], c[e], c[e + 1], s[e], s[e + 1], a, b2);
+                    ql[e / 2] = a;
+                    qh[e / 2] = b2;
+                }
                 if (ok) {
                     *(u32x2*)q = ql;
                     *(u32x2*)(q + HALF) = qh;

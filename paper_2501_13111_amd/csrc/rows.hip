@@ -245,13 +245,11 @@ __global__ void __launch_bounds__(256) rope_q_kernel(const float* __restrict__ q
         }
         const float2 c = *(const float2*)(cos_t + (int64_t)pos * half + j);
         const float2 s = *(const float2*)(sin_t + (int64_t)pos * half + j);
-        const float lo0 = __fsub_rn(__fmul_rn(u.x, c.x), __fmul_rn(v.x, s.x));
-        const float lo1 = __fsub_rn(__fmul_rn(u.y, c.y), __fmul_rn(v.y, s.y));
-        const float hi0 = __fadd_rn(__fmul_rn(v.x, c.x), __fmul_rn(u.x, s.x));
-        const float hi1 = __fadd_rn(__fmul_rn(v.y, c.y), __fmul_rn(u.y, s.y));
         uint16_t* q = qout + (((m / T) * nh + h) * T + pos) * d;
-        *(uint32_t*)(q + j) = F16 ? pack_f16_hw(lo0, lo1) : pack_bf16_hw(lo0, lo1);
-        *(uint32_t*)(q + j + half) = F16 ? pack_f16_hw(hi0, hi1) : pack_bf16_hw(hi0, hi1);
+        uint32_t lo, hi;
+        rotate_query<F16>(u.x, u.y, v.x, v.y, c.x, c.y, s.x, s.y, lo, hi);
+        *(uint32_t*)(q + j) = lo;
+        *(uint32_t*)(q + j + half) = hi;
     }
 }
 
@@ -307,8 +305,7 @@ __global__ void __launch_bounds__(NW * 64) kv_append_kernel(const float* __restr
                 }
             }
             const float c = cos_t[(int64_t)pos * half + j], s = sin_t[(int64_t)pos * half + j];
-            k0 = __fsub_rn(__fmul_rn(u, c), __fmul_rn(x, s));
-            k1 = __fadd_rn(__fmul_rn(x, c), __fmul_rn(u, s));
+            rotate_pair(u, x, c, s, k0, k1);
             if constexpr (!SPLIT) {
                 v0 = p[vcol + j];
                 v1 = p[vcol + j + half];
