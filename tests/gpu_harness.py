@@ -60,7 +60,7 @@ class ParityResult:
     chained_ref: np.ndarray = None  # the oracle's chained prefill output of the compared rows
 
 
-def run_parity(shape, wq, kvq, B, P, S, rows=None, seed=0, graph=True, acc=np.float64,
+def run_parity(shape, wq, kvq, B, P, S, rows=None, seed=0, acc=np.float64,
                oracle=None, fp=None, layerwise=False):
     """Prefill + S teacher-forced decode steps on the GPU and the oracle; compares
     sequences ``rows`` (all by default).  With ``layerwise`` the GPU also dumps every
@@ -75,7 +75,6 @@ def run_parity(shape, wq, kvq, B, P, S, rows=None, seed=0, graph=True, acc=np.fl
     own_fp = fp is None
     if own_fp:
         fp = Fingerprint(shape, wq, kvq, seed)
-    fp.set_decode_graph(graph)
     x = torch.empty(B * P * H, dtype=torch.bfloat16, device="cuda")
     fill_normal(x, seed, -1, fpgen.T_INPUT, 0.0, 1.0)
     y = torch.empty_like(x)

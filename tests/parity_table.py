@@ -43,7 +43,7 @@ def tables(recs):
         md.append("")
     full = [r for r in recs if r["kind"] == "fullsize"]
     if full:
-        md += ["### Full size (sampled sequences, graph-replayed decode to the cache's capacity)", "",
+        md += ["### Full size (sampled sequences, decode to the cache's capacity)", "",
                "| workload | rows | prefill error per layer | chained (bound; fp32-oracle drift) | decode max / last | KV max Δcode | KV mismatch rate |",
                "|---|---|---|---|---|---|---|"]
         md += [f"| {r['workload']} | {_fmt(r['rows'])} | {_fmt(r['prefill_layer_err'])} | "

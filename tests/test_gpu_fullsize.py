@@ -1,5 +1,6 @@
-"""Parity at the workloads' full sizes, in the launch configuration the benchmark times
-(the whole batch, prefill over the full prompt, every decode step replayed as a graph).
+"""Parity at the workloads' full sizes, in the launch configuration the benchmark times: the
+whole batch, prefill over the full prompt, single decode steps against the oracle, and all the
+steps as one call (one graph) against single steps.
 
 The oracle computes sampled sequences one by one (sequences are independent): the
 first and / or last of the batch.  Teacher forcing as everywhere: each prefill layer
@@ -59,7 +60,7 @@ def test_full_size_sampled_sequences(name, rows):
     log(f"full size {name}: B={c['B']} P={c['P']} S={c['S']} rows={rows}")
     orc = OracleFingerprint(s, c["wq"], c["kvq"], 0)
     fp = Fingerprint(s, c["wq"], c["kvq"], 0)
-    res = run_parity(s, c["wq"], c["kvq"], c["B"], c["P"], c["S"], rows=rows, graph=True, layerwise=True,
+    res = run_parity(s, c["wq"], c["kvq"], c["B"], c["P"], c["S"], rows=rows, layerwise=True,
                      oracle=orc, fp=fp)
     kv = None
     if c["kvq"] == "int8":
@@ -90,6 +91,39 @@ def test_full_size_sampled_sequences(name, rows):
     assert res.prefill_err <= bound
     if kv is not None:
         assert max(m for m, _ in kv) <= 1 and max(r for _, r in kv) <= 1e-3
+
+
+@pytest.mark.parametrize("name", [f[0] for f in FULL])
+def test_full_size_steps_in_one_call_match_single_steps(name):
+    """All decode steps of the workload as one call, captured and replayed as a graph on the
+    full-size grids, equal chained single steps bit for bit, in both buffers: on the capture and
+    on a second replay after another prompt."""
+    import torch
+    from paper_2501_13111_amd import Fingerprint, fill_normal
+    c = CONFIGS[name]
+    s, B, P, S = c["shape"], c["B"], c["P"], c["S"]
+    log(f"full size steps {name}: B={B} P={P} S={S}")
+    with Fingerprint(s, c["wq"], c["kvq"], 0) as fp:
+        x = torch.empty(B * P * s.hidden, dtype=torch.bfloat16, device="cuda")
+        y = torch.empty_like(x)
+        a, b, u, v = (torch.empty(B, s.hidden, dtype=torch.bfloat16, device="cuda") for _ in range(4))
+        for seed in (0, 1):
+            fill_normal(x, seed, -1, 15, 0.0, 1.0)
+            fp.prefill(x, y, B, P)
+            u.copy_(y.view(B, P, s.hidden)[:, -1, :])
+            p, q = u, v
+            for _ in range(S):
+                fp.decode_step(p, q)
+                p, q = q, p
+            torch.cuda.synchronize()
+            fp.prefill(x, y, B, P)
+            a.copy_(y.view(B, P, s.hidden)[:, -1, :])
+            out = fp.decode_steps(a, b, S)
+            torch.cuda.synchronize()
+            other = b if out is a else a
+            assert bool(torch.isfinite(out).all()) and fp.position() == (s.max_seq, B)
+            assert torch.equal(out.view(torch.int16), p.view(torch.int16)), seed
+            assert torch.equal(other.view(torch.int16), q.view(torch.int16)), seed
 
 
 @pytest.mark.timeout(900)

@@ -142,26 +142,32 @@ def test_parity_reduced(case):
     assert max(res.decode_errs) <= TOL
 
 
-def test_graph_replay_matches_eager():
+@pytest.mark.parametrize("B,wq", [(2, "int8"), (1, "int4"), (3, "sp24"), (1, "sp24")])
+def test_graph_replay_matches_eager(B, wq):
+    """Runs of decode steps replayed as one graph against the same runs launched one by one, bit
+    for bit: the same captured graph three times, at later positions and after another prefill,
+    with the test's own work and synchronisations between the replays."""
     import torch
     from paper_2501_13111_amd import Fingerprint, fill_normal
-    shape = Shape(2, 256, 4, 2, 64, 384, 2, 40, 48)
+    H, P = 512, 40
     outs = {}
     for graph in (False, True):
-        with Fingerprint(shape, "int8", "int8", seed=3) as fp:
+        log(f"graph replay {wq} B={B} graph={graph}")
+        with Fingerprint(Shape(2, H, 8, 2, 64, 768, B, P, P + 9), wq, "int8", seed=3) as fp:
             fp.set_decode_graph(graph)
-            x = torch.empty(2 * 40 * 256, dtype=torch.bfloat16, device="cuda")
-            fill_normal(x, 3, -1, 15, 0.0, 1.0)
+            x = torch.empty(B * P * H, dtype=torch.bfloat16, device="cuda")
             y = torch.empty_like(x)
-            fp.prefill(x, y, 2, 40)
-            a = y.view(2, 40, 256)[:, -1, :].contiguous()
-            b = torch.empty_like(a)
+            a, b = (torch.empty(B, H, dtype=torch.bfloat16, device="cuda") for _ in range(2))
             res = []
-            for s in range(6):
-                fp.decode_step(a, b)
-                torch.cuda.synchronize()
-                res.append(b.clone())
-                a, b = b, a
+            for seed in (3, 11):
+                fill_normal(x, seed, -1, 15, 0.0, 1.0)
+                fp.prefill(x, y, B, P)
+                a.copy_(y.view(B, P, H)[:, -1, :])
+                for _ in range(3):
+                    out = fp.decode_steps(a, b, 3)       # ends in b: the same (a, b, 3) every time
+                    res += [out.clone(), a.clone()]
+                    torch.cuda.synchronize()
+                    a.copy_(out)
             outs[graph] = torch.stack(res).cpu()
     assert torch.equal(outs[False].view(torch.int16), outs[True].view(torch.int16))
 
@@ -200,8 +206,10 @@ def test_single_steps_with_inner_layers_as_a_graph(wq, kvq):
     assert all(torch.equal(u, v) for u, v in zip(outs[False], outs[True]))
 
 
-@pytest.mark.parametrize("B,wq,kvq", [(3, "int4", "int8"), (1, "bf16", "bf16"), (1, "int8", "int8")],
-                         ids=["batch3-int4-int8kv", "single-bf16", "single-int8-int8kv"])
+@pytest.mark.parametrize("B,wq,kvq", [(3, "int4", "int8"), (1, "bf16", "bf16"), (1, "int8", "int8"),
+                                         (3, "sp24", "bf16"), (1, "sp24", "int8")],
+                         ids=["batch3-int4-int8kv", "single-bf16", "single-int8-int8kv", "batch3-sp24",
+                              "single-sp24-int8kv"])
 def test_decode_steps_match_single_steps(B, wq, kvq):
     """n steps in one call (one graph) give bit for bit what n calls of fp_decode_step
     give, with the decode graph on and off, for odd and even n, the batch schedule and the
@@ -312,8 +320,8 @@ def test_kv_codes_end_to_end_within_one():
 
 
 def test_reprefill_with_another_batch_drops_stale_graphs():
-    """Decode graphs are captured per (x, y, batch).  Prefill B = 3, graph decode steps,
-    then prefill B = 2 and B = 1 on the same handle and the same x / y buffers (sized for
+    """Graphs of several decode steps are captured per (x, y, n, batch).  Prefill B = 3, single
+    steps and two steps as a graph, then prefill B = 2 and B = 1 on the same handle and the same x / y buffers (sized for
     the largest batch, with sentinel rows past the active batch): every decode output
     equals a fresh handle's bit for bit, and the rows past the active batch are never
     written."""
