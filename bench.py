@@ -45,11 +45,11 @@ PROJ = {"qkv", "o", "gate_up", "down"}
 # were taken on (hash of the kernel's source files and of its argument block in
 # fp_internal.h); the summaries and commands are in profiles/.
 TRAFFIC = {
-    ("prefill_gemm", "llama2-70b-tp8-int4"): {"src": "fe37974026cf516b", "bytes_per_launch": 8838799402},
-    ("prefill_attn", "llama2-70b-tp8-int4"): {"src": "728c82f264714b03", "bytes_per_launch": 1623881112},
-    ("decode_proj", "llama2-70b-tp8-int4"): {"src": "7bbc74de5f69e243", "bytes_per_launch": 27162885},
-    ("decode_attn", "llama2-70b-tp8-int4"): {"src": "5240dca1acd310c1", "bytes_per_launch": 47376932},
-    ("decode_proj", "llama2-7b-bf16"): {"src": "7bbc74de5f69e243", "bytes_per_launch": 102930905},
+    ("prefill_gemm", "llama2-70b-tp8-int4"): {"src": "1aa33d99a8a46f85", "bytes_per_launch": 8864941591},
+    ("prefill_attn", "llama2-70b-tp8-int4"): {"src": "df226b5255b67aca", "bytes_per_launch": 1623948795},
+    ("decode_proj", "llama2-70b-tp8-int4"): {"src": "87db6def813c13db", "bytes_per_launch": 27162884},
+    ("decode_attn", "llama2-70b-tp8-int4"): {"src": "69e5aa2346d859f4", "bytes_per_launch": 47375657},
+    ("decode_proj", "llama2-7b-bf16"): {"src": "87db6def813c13db", "bytes_per_launch": 102930906},
 }
 FAMILY_SRC = {
     "decode_proj": (("skinny.hip", "fp_device.h"), r"enum XForm \{.*?\n\};\n.*?struct SkinnyArgs \{.*?\n\};"),

@@ -621,7 +621,7 @@ def test_parity_large_prompt_split(wq, kvq, H, F, B, P, want):
     assert all(w is None or (g > 1) == bool(w) for g, w in zip(got, want)), got
     res = run_parity(Shape(2, H, H // 128, 2, 128, F, B, P, P + 2), wq, kvq, B, P, 1, layerwise=True,
                      rows=sorted({0, B - 1}))
-    _report(f"large-split-{wq}-{H}", res)
+    _report(f"large-split-{wq}-{H}-{B}x{P}", res)
     assert res.prefill_err <= TOL
     assert all(e <= TOL for e in res.layer_errs)
     assert max(res.decode_errs) <= TOL
